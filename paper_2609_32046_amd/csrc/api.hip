@@ -91,6 +91,7 @@ int prepare_score(const void* q, const void* k, const cb_layout* lay, float* imp
   a->importance = importance;
   a->row_lse = row_lse;
   a->partial = reinterpret_cast<float2*>(w + p->off_partial);
+  a->lse2 = p->off_lse2 ? reinterpret_cast<float*>(w + p->off_lse2) : nullptr;
   a->imp_partial = reinterpret_cast<float*>(w + p->off_imp_partial);
   a->numer_partial = reinterpret_cast<float*>(w + p->off_numer_partial);
   a->sync = reinterpret_cast<uint32_t*>(w + p->off_sync);

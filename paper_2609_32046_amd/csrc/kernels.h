@@ -82,7 +82,7 @@ struct ScorePlan {
   bool position;    // position-level variant
   int Gp;           // padded group (position variant), else G
   int Rp;           // rows the kernel iterates per unit: R, or Gp*m
-  int chunks;       // ceil(T / kMinChunkTokens): the workspace holds this many
+  int chunks;       // chunks per unit the workspace holds
   int rb;           // 16-row MFMA blocks per wave: 4, or 5 (see make_score_plan)
   SelectSplit sel;  // split selection of the same units (cb_pipeline)
   size_t off_sel_counters;   // in words from the sync words' start
@@ -90,7 +90,7 @@ struct ScorePlan {
   int row_groups;   // ceil(Rp / (16 * rb * kMaxWaves))
   int waves;        // waves per workgroup
   float c2;         // scale * log2(e)
-  size_t off_partial, off_imp_partial, off_numer_partial, off_sync, sync_words, total_bytes;
+  size_t off_partial, off_lse2, off_imp_partial, off_numer_partial, off_sync, sync_words, total_bytes;
 };
 
 bool make_score_plan(int L, int Hq, int Hkv, int D, int m, int S, int64_t T, int dtype,
@@ -112,6 +112,7 @@ struct PersistArgs {
   float* importance;     // [U][T]
   float* row_lse;        // [U][R] or null
   float2* partial;       // [U][chunks][Rp]: per-chunk (max, sum) of each row, log2 units
+  float* lse2;           // [U][Rp]: log2 of the row normalisers (one-item workgroups), or null
   float* imp_partial;    // [row_groups][U][T] when row_groups > 1
   // Position variant: per unit and position, the sum over query tokens r of
   // P^p * 2^kappa (or the maximum of P), where P is Pool_7 over positions of
@@ -130,6 +131,7 @@ struct PersistArgs {
   int chunk_tokens;      // positions per score item
   int chunks, row_groups, units;   // chunks = ceil(T / chunk_tokens)
   float c2;
+  int sync_words;        // words at `sync` the first pass clears (one-item workgroups)
   uint32_t spin_limit;   // polls before a dependency wait gives up
   WorkList wl;
 };

@@ -74,28 +74,43 @@ bool make_score_plan(int L, int Hq, int Hkv, int D, int m, int S, int64_t T, int
     p->Gp = G;
     p->Rp = p->R;
   }
-  p->chunks = (int)((T + kMinChunkTokens - 1) / kMinChunkTokens);
-  // Waves of 64 rows in a power-of-two workgroup, except that a unit of 257
-  // to 320 rows (five query heads per KV head at m = 64) takes four waves of
-  // 80 rows (five MFMA row blocks): as five waves of an eight-wave workgroup
-  // it would leave three waves idle and, at two waves per SIMD, one SIMD
-  // with twice the rows of the others.
-  if (!position && p->Rp > 4 * kRowsPerWave && p->Rp <= 4 * 80) {
-    p->rb = 5;
-    p->row_groups = 1;
-    p->waves = 4;
-  } else {
-    p->rb = 4;
-    p->row_groups = (p->Rp + kRowsPerGroup - 1) / kRowsPerGroup;
-    const int rows0 = p->Rp < kRowsPerGroup ? p->Rp : kRowsPerGroup;
-    const int need = (rows0 + kRowsPerWave - 1) / kRowsPerWave;
-    p->waves = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : 8;
+  // Waves per workgroup (a power of two, so that workgroups spread evenly over
+  // the four SIMDs) and 16-row MFMA blocks per wave: the smallest that hold
+  // the rows, up to 512 rows a workgroup.  Rows padded to 64 per wave cost
+  // as much as real ones: 36 x 8 units of 160 rows (three blocks in four waves
+  // instead of four) 630 -> 493 us as a whole position-level call.
+  static constexpr int kShapes[][2] = {{1, 1}, {1, 2}, {1, 3}, {1, 4}, {2, 3}, {2, 4}, {4, 3},
+                                       {4, 4}, {4, 5}, {8, 4}};
+  p->row_groups = (p->Rp + kRowsPerGroup - 1) / kRowsPerGroup;
+  for (const auto& sh : kShapes) {
+    if ((dtype == 0 && sh[1] == 3) || (position && sh[1] == 5)) continue;
+    p->waves = sh[0];
+    p->rb = sh[1];
+    if (16 * sh[0] * sh[1] >= p->Rp) break;
+  }
+  // Chunks: as many as fill 2048 workgroups, of no fewer than kTileTokens
+  // positions, or else those of kMinChunkTokens.
+  {
+    const int64_t groups = (int64_t)p->units * p->row_groups;
+    const int64_t least = (T + kMinChunkTokens - 1) / kMinChunkTokens;
+    int64_t c = (2048 + groups - 1) / groups;
+    const int64_t most = (T + kTileTokens - 1) / kTileTokens;
+    if (c > most) c = most;
+    if (c > 512) c = 512;
+    p->chunks = (int)(c > least ? c : least);
   }
   const float sc = scale > 0.f ? scale : (float)(1.0 / sqrt((double)D));
   p->c2 = (float)((double)sc * 1.4426950408889634);
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   size_t off = 0;
   p->off_partial = off; off = al(off + (size_t)p->units * p->chunks * p->Rp * sizeof(float2));
+  // Row normalisers between the two launches: only calls small enough for
+  // that form (launch_w) with many chunks a unit.
+  p->off_lse2 = 0;
+  if (p->chunks > 16 && (int64_t)p->units * p->row_groups * p->chunks <= 4096) {
+    p->off_lse2 = off;
+    off = al(off + (size_t)p->units * p->Rp * sizeof(float));
+  }
   p->off_imp_partial = off;
   if (p->row_groups > 1) off = al(off + (size_t)p->row_groups * p->units * (size_t)T * sizeof(float));
   p->off_numer_partial = off;

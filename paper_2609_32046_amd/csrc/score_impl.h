@@ -15,6 +15,10 @@
 //                 lse2 (log2 of the row normaliser), recompute the logits and
 //                 add exp2(x - lse2) over the rows.
 //
+// Calls too small to fill the device for long run P1 and P2 as two plain
+// launches of one item per workgroup (pass_kernel; the rule is in launch_w).
+// The rest run as one persistent kernel:
+//
 // Scheduling.  Every P1 and P2 item of every unit sits in one ordered list
 // (WorkList in kernels.h); resident workgroups take items from a device
 // queue (one atomic counter) until the list is exhausted.  A P2 item waits
@@ -37,8 +41,8 @@
 //
 // Score items run the contraction on bf16 (fp32 for fp32 inputs) MFMA with
 // fp32 accumulation.  Each wavefront holds 16*RB query rows in registers
-// (RB = 4 row blocks; 5 when a unit has 257 to 320 rows, so that four
-// waves cover it instead of five of eight);
+// (RB = 1 to 5 row blocks, so that a unit's rows fill one, two or four waves
+// with few padding rows; make_score_plan);
 // K tiles of 64 or 128 positions are staged through an LDS ring (XOR-swizzled 16-byte
 // chunks so B-fragment reads are bank-conflict free) and shared by every
 // wave of the workgroup.  The contraction index is permuted consistently for
@@ -62,10 +66,13 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // K positions per LDS tile: 128 for bf16 workgroups of four or more waves
 // (half the per-tile barrier, wait and address work per position, two
-// 32 KiB ring stages), else kTileTokens.
-template <int ESZ, int W>
+// 32 KiB ring stages), 8 KiB for one-wave workgroups (so that eight of them,
+// two waves per SIMD, fit the 160 KiB LDS; 16 KiB tiles left one), but no less
+// than two column blocks, else kTileTokens.
+template <int ESZ, int D, int W>
 struct TileTokens {
-  static constexpr int value = (ESZ == 2 && W >= 4) ? 2 * kTileTokens : kTileTokens;
+  static constexpr int value = W == 1 ? (8192 / (D * ESZ) < 32 ? 32 : 8192 / (D * ESZ))
+                               : (ESZ == 2 && W >= 4) ? 2 * kTileTokens : kTileTokens;
 };
 
 template <int ESZ, int D, int TT>
@@ -132,10 +139,10 @@ __device__ __forceinline__ void mfma_seg<4>(const u32x4& a, const u32x4& b, f32x
 // after the other LDS arrays.
 template <int ESZ, int D, int W, bool POS, int RB = 4>
 struct Stages {
-  static constexpr int kTT = TileTokens<ESZ, W>::value;
+  static constexpr int kTT = TileTokens<ESZ, D, W>::value;
   static constexpr int kTile = kTT * D * ESZ;
   static constexpr int kOther = W * ((POS ? 5 : 2) * kTT + 16 * RB) * 4;
-  static constexpr int kBudget = (W >= 2 ? 160 * 1024 * W / 8 : 40 * 1024) - kOther;
+  static constexpr int kBudget = 160 * 1024 * W / 8 - kOther;
   static constexpr int kFit = kBudget / kTile;
   static constexpr int value = kFit < 2 ? 2 : (kFit > 4 ? 4 : kFit);
 };
@@ -387,7 +394,7 @@ __device__ __forceinline__ Item decode(const WorkList& wl, int64_t item) {
 // LDS of one workgroup, shared by every item type.
 template <int ESZ, int D, int W, bool POS, int RB = 4>
 struct Shared {
-  static constexpr int kTT = TileTokens<ESZ, W>::value;
+  static constexpr int kTT = TileTokens<ESZ, D, W>::value;
   using Gm = Geo<ESZ, D, kTT>;
   static constexpr int kStages = Stages<ESZ, D, W, POS, RB>::value;
   unsigned char ktile[kStages][Gm::kTileBytes] __attribute__((aligned(16)));
@@ -418,15 +425,14 @@ __device__ __forceinline__ bool real_row(const PersistArgs& a, int rho, int* qro
 // PM (position variant): 0 reads the power mode and head grouping from the
 // arguments; 1 fixes p = 2 and groups of four query heads at compile time,
 // so the per-block pooling epilogue has no run-time branches.
-template <int ESZ, int D, int W, int RB, bool PASS2, bool POS, int PM = 0>
+template <int ESZ, int D, int W, int RB, bool PASS2, bool POS, int PM = 0, bool STATIC = false>
 __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
                                            Shared<ESZ, D, W, POS, RB>& sh) {
   const int pow_mode = PM == 1 ? (int)kPowSquare : a.pow_mode;
   const int gshift = PM == 1 ? 2 : a.gshift;
-  static_assert(RB == 4 || (RB == 5 && !POS), "five row blocks only for the importance path");
   constexpr int kRPW = 16 * RB;                  // query rows per wave
   constexpr int kGroupRows = kRPW * kMaxWaves;   // rows per row group
-  constexpr int TT = TileTokens<ESZ, W>::value;   // positions per K tile
+  constexpr int TT = TileTokens<ESZ, D, W>::value;   // positions per K tile
   using Gm = Geo<ESZ, D, TT>;
   constexpr int kBlocks = Gm::kBlocks;
   constexpr int kPer = Gm::kTileChunks / (W * 64);   // 16-byte loads per thread per tile
@@ -466,12 +472,33 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   // are folded in ascending order, eight loads in flight, so every workgroup
   // of the unit derives bitwise-identical lse2.
   if (PASS2) {
-    const bool ok = wait_for(done1 + (size_t)u * a.row_groups + rg, (uint32_t)a.chunks,
-                             a.sync + kSyncError, a.spin_limit, &sh.ok);
+    bool ok;
+    if constexpr (STATIC) {
+      // The statistics were written by an earlier launch: nothing to wait
+      // for, and only a wait limit of 0 gives up.
+      ok = a.spin_limit != 0u;
+      if (tid == 0) {
+        sh.ok = ok;
+        if (!ok)
+          __hip_atomic_fetch_or(a.sync + kSyncError, 1u, __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_AGENT);
+      }
+    } else {
+      ok = wait_for(done1 + (size_t)u * a.row_groups + rg, (uint32_t)a.chunks,
+                    a.sync + kSyncError, a.spin_limit, &sh.ok);
+    }
     const int row_base = rg * kGroupRows;
     const int nrows = (a.Rp - row_base < W * kRPW) ? a.Rp - row_base : W * kRPW;
     for (int lr = tid; lr < nrows; lr += W * 64) {
       const int row = row_base + lr;
+      if (STATIC && a.lse2) {
+        const float l2 = ok ? a.lse2[(size_t)u * a.Rp + row] : __builtin_nanf("");
+        lse_lds[lr] = l2;
+        int qrow;
+        if (chunk == 0 && a.row_lse && real_row<POS>(a, row, &qrow))
+          a.row_lse[(size_t)u * a.R + qrow] = l2 * 0.69314718055994530942f;
+        continue;
+      }
       const float2* p = a.partial + (size_t)u * a.chunks * a.Rp + row;
       float m = -INFINITY, z = 0.f;
       int c = 0;
@@ -634,10 +661,12 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     load_block(kt, tb, kf);
     mfma_block(kf, acc);
   };
-  // Software pipeline over the four column blocks of a tile: the LDS reads
+  // Software pipeline over the column blocks of a tile: the LDS reads
   // and MFMAs of block tb+1 are issued ahead of block tb's exp epilogue, and
   // the scheduler is asked to interleave them, so the matrix unit and the
-  // VALU work at the same time within one wave.
+  // VALU work at the same time within one wave.  (Not for fp32, which waits on
+  // its 32-cycle MFMAs: the hints gain nothing and cost minutes of compile
+  // time.)
   constexpr int kMfmaPerBlock = RB * Gm::kSegs * (ESZ == 4 ? 4 : 1);
   auto pipelined_tile = [&](const unsigned char* kt, auto&& epilogue) {
     u32x4 kf[2][Gm::kSegs];
@@ -652,7 +681,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
         mfma_block(kf[cur ^ 1], acc[cur ^ 1]);
       }
       epilogue(tb, acc[cur]);
-      if (tb < kBlocks - 1) interleave_mfma_valu<kMfmaPerBlock, 3>();
+      if (ESZ == 2 && tb < kBlocks - 1) interleave_mfma_valu<kMfmaPerBlock, 3>();
     }
   };
 
@@ -665,27 +694,27 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   // of a DPP row and into the neighbouring blocks: a block is finalised when
   // the next block is known, from its left4/right4 parts; the blocks beyond
   // the chunk's two ends are computed separately from K in global memory.
-  uint32_t r4p[4] = {0u, 0u, 0u, 0u};   // right4 of the previous block
-  uint32_t pc[4] = {0u, 0u, 0u, 0u};    // previous block pooled, except the next block's part
+  uint32_t r4p[RB] = {};   // right4 of the previous block
+  uint32_t pc[RB] = {};    // previous block pooled, except the next block's part
   auto head_sum = [&](float v) { return gshift == 3 ? sum_lane_pairs(v) : v; };
   // Numerator terms of a finalised block, summed over this wave's tokens
   // (or their maximum at p = inf), into the tile's LDS slot.
-  auto store_numer = [&](int btile, int btb, const uint32_t(&fin)[4]) {
+  auto store_numer = [&](int btile, int btb, const uint32_t(&fin)[RB]) {
     float acc = 0.f;
     if (pow_mode == kPowSquare) {
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
+      for (int rb = 0; rb < RB; ++rb) {
         const float t = __uint_as_float(fin[rb]) * a.sq_scale;
         acc = __builtin_fmaf(t, t, acc);
       }
     } else if (pow_mode == kPowGeneral) {
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb)
+      for (int rb = 0; rb < RB; ++rb)
         acc += __builtin_amdgcn_exp2f(__builtin_fmaf(
             a.pow_p, __builtin_amdgcn_logf(__uint_as_float(fin[rb])), a.pow_kappa));
     } else {
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) acc = fmaxf(acc, __uint_as_float(fin[rb]));
+      for (int rb = 0; rb < RB; ++rb) acc = fmaxf(acc, __uint_as_float(fin[rb]));
     }
     if (pow_mode == kPowMax) {
       acc = max_lane_groups(acc);
@@ -696,10 +725,10 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     if (lg == 0) sh.num[POS ? btile % 3 : 0][wave][POS ? btb * 16 + lc : 0] = acc;
   };
   // Pool a new block x: finalise the previous one, keep this one's parts.
-  auto pool_block = [&](const uint32_t(&x)[4], int tile, int tb) {
-    uint32_t fin[4];
+  auto pool_block = [&](const uint32_t(&x)[RB], int tile, int tb) {
+    uint32_t fin[RB];
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
+    for (int rb = 0; rb < RB; ++rb) {
       const uint32_t l4 = left4(x[rb]), r4 = right4(x[rb]);
       fin[rb] = umax(pc[rb], row_shr<13>(l4));   // lanes 13..15 see this block's 0..2
       pc[rb] = umax(umax(l4, r4), row_shl<13>(r4p[rb]));   // lanes 0..2 see 13..15 before
@@ -713,7 +742,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   };
   // Weights of the block of 16 positions from tstart, from K in global memory
   // (positions outside [0, T) weigh 0).
-  auto halo_bits = [&](int64_t tstart, uint32_t(&x)[4]) {
+  auto halo_bits = [&](int64_t tstart, uint32_t(&x)[RB]) {
     const int64_t row = tstart + lc;
     const bool okr = row >= 0 && row < a.T;
     const u32x4* src = reinterpret_cast<const u32x4*>(kb + (size_t)(okr ? row : 0) *
@@ -724,7 +753,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     f32x4 acc[RB];
     mfma_block(kf, acc);
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
+    for (int rb = 0; rb < RB; ++rb) {
       float p = 0.f;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -747,10 +776,10 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     __syncthreads();   // every row's lse2 is in LDS
     load_row_l2();
     if (wave_active && t_begin > 0) {
-      uint32_t hx[4];
+      uint32_t hx[RB];
       halo_bits(t_begin - 16, hx);
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) r4p[rb] = right4(hx[rb]);
+      for (int rb = 0; rb < RB; ++rb) r4p[rb] = right4(hx[rb]);
     }
   }
 
@@ -770,7 +799,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     if (tile + kStages - 1 < ntiles) issue_tile(tile + kStages - 1, (tile + kStages - 1) % kStages);
     // The next item is taken while the last tile is computed; no ring load
     // is in flight any more, so its latency hides behind the tile.
-    if (tile == ntiles - 1 && tid == 0) next = take_item(a.sync);
+    if (!STATIC && tile == ntiles - 1 && tid == 0) next = take_item(a.sync);
     if (PASS2 && !POS && tile == 0) load_row_l2();
     // P2: the previous tile's per-wave column sums are complete; they are
     // added in wave order and the tile's importance is stored.  Numerators
@@ -801,16 +830,21 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
             p += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[rb][i], a.c2, -row_l2[rb][i]));
           part[rb] = p;
         }
-        float psum = (part[0] + part[1]) + (part[2] + part[3]);
+        float psum = part[0];
+        if constexpr (RB >= 2) psum += part[1];
+        if constexpr (RB >= 4)
+          psum += part[2] + part[3];
+        else if constexpr (RB == 3)
+          psum += part[2];
 #pragma unroll
         for (int rb = 4; rb < RB; ++rb) psum += part[rb];
         const float sum = sum_lane_groups(psum);
         if (lg == 0) dst[tb * 16] = sum;
         if constexpr (POS) {
           const bool okp = tok0 + tb * 16 + lc < a.T;
-          uint32_t x[4];
+          uint32_t x[RB];
 #pragma unroll
-          for (int rb = 0; rb < 4; ++rb) x[rb] = okp ? __float_as_uint(head_sum(part[rb])) : 0u;
+          for (int rb = 0; rb < RB; ++rb) x[rb] = okp ? __float_as_uint(head_sum(part[rb])) : 0u;
           pool_block(x, tile, tb);
         }
       });
@@ -899,11 +933,11 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   }
   if (PASS2 && POS && wave_active) {
     // the chunk's last block: its right neighbour is the next chunk's first
-    uint32_t hx[4] = {0u, 0u, 0u, 0u};
+    uint32_t hx[RB] = {};
     if (t_end < a.T) halo_bits(t_end, hx);
-    uint32_t fin[4];
+    uint32_t fin[RB];
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) fin[rb] = umax(pc[rb], row_shr<13>(left4(hx[rb])));
+    for (int rb = 0; rb < RB; ++rb) fin[rb] = umax(pc[rb], row_shr<13>(left4(hx[rb])));
     store_numer(ntiles - 1, kBlocks - 1, fin);
   }
   __syncthreads();
@@ -914,10 +948,12 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       if (ntiles > 1) flush_num(ntiles - 2);
       flush_num(ntiles - 1);
     }
-    stores_done_barrier();
-    if (tid == 0) {
-      count_in(done2 + u);
-      sh.next = next;
+    if constexpr (!STATIC) {
+      stores_done_barrier();
+      if (tid == 0) {
+        count_in(done2 + u);
+        sh.next = next;
+      }
     }
     return;
   }
@@ -944,10 +980,12 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       if (lc == 0 && row < a.Rp)
         put_f2(a.partial + ((size_t)u * a.chunks + chunk) * a.Rp + row, make_float2(m, z));
     }
-  stores_done_barrier();
-  if (tid == 0) {
-    count_in(done1 + (size_t)u * a.row_groups + rg);
-    sh.next = next;
+  if constexpr (!STATIC) {
+    stores_done_barrier();
+    if (tid == 0) {
+      count_in(done1 + (size_t)u * a.row_groups + rg);
+      sh.next = next;
+    }
   }
 }
 
@@ -973,6 +1011,56 @@ __global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void persistent_kernel(Pe
   }
 }
 
+// One score pass of every item, one item per workgroup: blocks of one unit go
+// to the same XCD (workgroups are dealt to the eight XCDs in turn), whose L2
+// then serves its query rows.  The second pass takes the items last first, so
+// that it starts on the keys the first pass read last.
+template <int ESZ, int D, int W, bool POS, int RB, int PM, bool PASS2>
+__global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void pass_kernel(PersistArgs a) {
+  __shared__ Shared<ESZ, D, W, POS, RB> sh;
+  if (!PASS2)   // the words later launches of the call count in
+    for (int i = blockIdx.x * (W * 64) + threadIdx.x; i < a.sync_words; i += gridDim.x * (W * 64))
+      a.sync[i] = 0u;
+  const int per_unit = a.chunks * a.row_groups;
+  const int n = a.units * per_unit;
+  int item = (int)(blockIdx.x & 7u) * ((int)gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  if (item >= n) return;
+  if (PASS2) item = n - 1 - item;
+  const int u = item / per_unit;
+  score_item<ESZ, D, W, RB, PASS2, POS, PM, true>(a, u, item - u * per_unit, sh);
+}
+
+// lse2[row] of every query row from its chunks' (max, sum) pairs: eight
+// threads a row, each folding every eighth chunk with eight loads in flight.
+__global__ __launch_bounds__(256) void fold_stats(const float2* __restrict__ partial,
+                                                  float* __restrict__ lse2, int chunks, int Rp,
+                                                  int64_t rows) {
+  __shared__ float2 part[8][32];
+  const int r = threadIdx.x & 31, k = threadIdx.x >> 5;
+  const int64_t row = (int64_t)blockIdx.x * 32 + r;
+  float m = -INFINITY, z = 0.f;
+  if (row < rows) {
+    const int64_t u = row / Rp;
+    const float2* p = partial + (size_t)u * chunks * Rp + (row - u * Rp);
+    for (int c0 = k; c0 < chunks; c0 += 64) {
+      float2 v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int c = c0 + 8 * j;
+        v[j] = c < chunks ? p[(size_t)c * Rp] : make_float2(-INFINITY, 0.f);
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) lse_merge(m, z, v[j].x, v[j].y);
+    }
+  }
+  part[k][r] = make_float2(m, z);
+  __syncthreads();
+  if (k != 0 || row >= rows) return;
+#pragma unroll
+  for (int j = 1; j < 8; ++j) lse_merge(m, z, part[j][r].x, part[j][r].y);
+  lse2[row] = m + __log2f(z);
+}
+
 // out[u][t] = sum (or maximum) over row groups, in order.
 __global__ void rowgroup_sum(const float* __restrict__ part, float* __restrict__ out,
                              int row_groups, int64_t per_group, int64_t n, int take_max) {
@@ -992,8 +1080,27 @@ __global__ void zero_words(uint32_t* __restrict__ p, int64_t n) {
 
 // Resident workgroups per CU of one kernel instantiation, cached per device.
 std::mutex g_occ_mu;
-int g_occ[64][2][2][4][2][2][2];
+int g_occ[64][2][2][4][2][8][2];
 int g_cus[64];
+
+// Row-group partial sums of a call into its outputs.
+template <bool POS>
+hipError_t finish_row_groups(const ScorePlan& p, const PersistArgs& a, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  if (p.row_groups > 1) {
+    const int64_t n = (int64_t)p.units * p.T;
+    rowgroup_sum<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a.imp_partial, a.importance,
+                                                            p.row_groups, n, n, 0);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (POS) {
+      rowgroup_sum<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(
+          a.numer_partial, a.numer, p.row_groups, n, n, a.pow_mode == kPowMax);
+      e = hipGetLastError();
+    }
+  }
+  return e;
+}
 
 template <int ESZ, int D, int W, bool POS, int RB = 4, int PM = 0>
 hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
@@ -1005,7 +1112,7 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
   int per_cu = 0, cus = 0;
   {
     std::lock_guard<std::mutex> lock(g_occ_mu);
-    int& occ = g_occ[dev][ESZ == 2][D == 128][wi][POS][RB == 5][PM];
+    int& occ = g_occ[dev][ESZ == 2][D == 128][wi][POS][RB][PM];
     if (occ == 0) {
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
           &occ, reinterpret_cast<const void*>(&persistent_kernel<ESZ, D, W, POS, RB, PM>), W * 64, 0);
@@ -1026,6 +1133,40 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
   // the first round and every P2 item in the second, with nothing to overlap
   // the second pass's re-reads of K (8 layers x 8 KV heads x 65536
   // positions: 476 us at 2048 positions against 512 us at 4096).
+  // Calls whose items of kMinChunkTokens positions would not occupy the
+  // resident workgroups twice over run as two plain launches instead: the
+  // chunk is cut so that one item per resident workgroup covers the call, and
+  // the launch boundary stands in for the queue, its clearing kernel (5 us) and
+  // the waits.  Whole calls against the queue: one layer x 8 KV heads x
+  // 8192 positions 72.6 -> 40.8 us, 24 x 8 x 4096 with 32 rows 139 -> 85 us, the
+  // fp32 2 x 512 call 65 -> 22 us.  Above the line the queue's overlap of the two
+  // passes is worth more: 36 x 8 x 8192 (2304 items for 512 workgroups) 461 us
+  // queued, 490 us as two launches.
+  constexpr int TT = TileTokens<ESZ, D, W>::value;
+  const int64_t groups = (int64_t)p.units * p.row_groups;
+  if (groups * ((p.T + kMinChunkTokens - 1) / kMinChunkTokens) <= 2 * resident) {
+    int64_t c = (groups * p.T + resident - 1) / resident;
+    const int64_t least = (p.T + p.chunks - 1) / p.chunks;   // what the workspace holds
+    if (c < least) c = least;
+    c = (c + TT - 1) / TT * TT;
+    a.chunk_tokens = (int)c;
+    a.chunks = (int)((p.T + c - 1) / c);
+    // Folding up to 16 chunks in every second-pass workgroup costs less than
+    // a launch for it (8 chunks: 22.3 against 24.4 us for the whole call).
+    if (a.chunks <= 16) a.lse2 = nullptr;
+    a.sync_words = (int)p.sync_words;
+    const unsigned g = (unsigned)((groups * a.chunks + 7) / 8 * 8);
+    pass_kernel<ESZ, D, W, POS, RB, PM, false><<<g, W * 64, 0, s>>>(a);
+    if (a.lse2) {
+      const int64_t rows = (int64_t)p.units * p.Rp;
+      fold_stats<<<(unsigned)((rows + 31) / 32), 256, 0, s>>>(a.partial, a.lse2, a.chunks, a.Rp,
+                                                              rows);
+    }
+    pass_kernel<ESZ, D, W, POS, RB, PM, true><<<g, W * 64, 0, s>>>(a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return finish_row_groups<POS>(p, a, s);
+  }
   a.chunk_tokens = kMinChunkTokens;
   for (int c = kMaxChunkTokens; c > kMinChunkTokens; c /= 2)
     if ((int64_t)p.units * p.row_groups * ((p.T + c - 1) / c) > resident) {
@@ -1042,40 +1183,39 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
   persistent_kernel<ESZ, D, W, POS, RB, PM><<<(unsigned)grid, W * 64, 0, s>>>(a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (p.row_groups > 1) {
-    const int64_t n = (int64_t)p.units * p.T;
-    rowgroup_sum<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a.imp_partial, a.importance,
-                                                            p.row_groups, n, n, 0);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (POS) {
-      rowgroup_sum<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(
-          a.numer_partial, a.numer, p.row_groups, n, n, a.pow_mode == kPowMax);
-      e = hipGetLastError();
+  return finish_row_groups<POS>(p, a, s);
+}
+
+template <int ESZ, int D, bool POS, int PM>
+hipError_t launch_shape(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
+  switch (10 * p.waves + p.rb) {
+    case 11: return launch_w<ESZ, D, 1, POS, 1, PM>(p, a, s);
+    case 12: return launch_w<ESZ, D, 1, POS, 2, PM>(p, a, s);
+    case 14: return launch_w<ESZ, D, 1, POS, 4, PM>(p, a, s);
+    case 24: return launch_w<ESZ, D, 2, POS, 4, PM>(p, a, s);
+    case 44: return launch_w<ESZ, D, 4, POS, 4, PM>(p, a, s);
+    case 84: return launch_w<ESZ, D, 8, POS, 4, PM>(p, a, s);
+  }
+  if constexpr (ESZ == 2) {
+    switch (10 * p.waves + p.rb) {
+      case 13: return launch_w<ESZ, D, 1, POS, 3, PM>(p, a, s);
+      case 23: return launch_w<ESZ, D, 2, POS, 3, PM>(p, a, s);
+      case 43: return launch_w<ESZ, D, 4, POS, 3, PM>(p, a, s);
     }
   }
-  return e;
+  if constexpr (!POS) {
+    if (p.waves == 4 && p.rb == 5) return launch_w<ESZ, D, 4, POS, 5, PM>(p, a, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 template <int ESZ, int D, bool POS>
 hipError_t launch_d(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
-  if constexpr (!POS) {
-    if (p.rb == 5) return launch_w<ESZ, D, 4, POS, 5>(p, a, s);
-  } else if (a.pow_mode == kPowSquare && a.gshift == 2) {
-    // the paper's default score (p = 2) with four query heads per KV head
-    switch (p.waves) {
-      case 1: return launch_w<ESZ, D, 1, true, 4, 1>(p, a, s);
-      case 2: return launch_w<ESZ, D, 2, true, 4, 1>(p, a, s);
-      case 4: return launch_w<ESZ, D, 4, true, 4, 1>(p, a, s);
-      default: return launch_w<ESZ, D, 8, true, 4, 1>(p, a, s);
-    }
+  // the paper's default score (p = 2) with four query heads per KV head
+  if constexpr (POS) {
+    if (a.pow_mode == kPowSquare && a.gshift == 2) return launch_shape<ESZ, D, true, 1>(p, a, s);
   }
-  switch (p.waves) {
-    case 1: return launch_w<ESZ, D, 1, POS>(p, a, s);
-    case 2: return launch_w<ESZ, D, 2, POS>(p, a, s);
-    case 4: return launch_w<ESZ, D, 4, POS>(p, a, s);
-    default: return launch_w<ESZ, D, 8, POS>(p, a, s);
-  }
+  return launch_shape<ESZ, D, POS, 0>(p, a, s);
 }
 
 }  // namespace

@@ -1,0 +1,59 @@
+"""The score path's launch shapes on MI355X: row counts on both sides of every
+wave and row-block edge, and sequences on both sides of the tile, chunk and
+launch-count edges of the two-launch form, against the CPU oracle."""
+import numpy as np
+import pytest
+
+import cb_workloads as W
+from test_gpu_message import check_position, run_position
+from test_gpu_parity import cb, check_all_units, gen, orc, run_gpu, say, torch  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# (L, Hq, Hkv, D, T, m, S, dtype)
+SHAPES = [
+    # rows 1, 16 | 17, 32 | 33, 48 | 49, 64 (one wave, one to four blocks)
+    (1, 1, 1, 128, 33, 1, 1, "bf16"), (1, 4, 1, 64, 64, 4, 1, "bf16"),
+    (1, 1, 1, 128, 65, 17, 1, "bf16"), (2, 4, 2, 64, 1000, 16, 1, "bf16"),
+    (1, 3, 1, 128, 127, 11, 1, "bf16"), (1, 6, 2, 64, 129, 16, 2, "bf16"),
+    (1, 7, 1, 128, 256, 7, 1, "bf16"), (1, 8, 2, 64, 257, 16, 1, "bf16"),
+    # 65, 96 | 97, 128 (two waves), 129, 192 | 193, 256 | 257, 320 | 321 (four, eight)
+    (1, 5, 1, 128, 300, 13, 1, "bf16"), (1, 6, 1, 64, 513, 16, 1, "bf16"),
+    (1, 1, 1, 128, 128, 97, 1, "bf16"), (1, 3, 1, 128, 1025, 43, 1, "bf16"),
+    (1, 6, 1, 64, 640, 32, 1, "bf16"), (1, 1, 1, 128, 130, 193, 1, "bf16"),
+    (1, 1, 1, 64, 129, 257, 1, "bf16"), (1, 3, 1, 128, 200, 107, 1, "bf16"),
+    # more than 16 chunks a unit (the statistics folded by a launch of their
+    # own): 64 and 512 chunks, and two row groups
+    (1, 2, 1, 128, 4097, 8, 1, "bf16"), (1, 4, 1, 64, 40000, 4, 1, "bf16"),
+    (1, 8, 1, 128, 3000, 65, 1, "bf16"),
+    # fp32 in one, two and four blocks a wave
+    (1, 3, 1, 64, 97, 5, 1, "f32"), (1, 2, 1, 128, 33, 16, 2, "f32"),
+    (1, 3, 1, 128, 1100, 16, 1, "f32"), (1, 5, 1, 64, 700, 13, 1, "f32"),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_launch_shapes(torch, cb, orc, shape):   # noqa: F811
+    L, Hq, Hkv, D, T, m, S, dt = shape
+    w = W.custom(layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=D, q_len=m, seq_len=T, senders=S,
+                 dtype=dt, cfg_id=411)
+    say(f"case {shape}")
+    q, K, V = gen(w)
+    out = run_gpu(torch, cb, w, q, K, V, 0.25)
+    check_all_units(orc, w, q, K, V, out, what=str(shape))
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 2, 1, 128, 40, 3, 1, "bf16"), (1, 4, 1, 64, 1100, 8, 1, "bf16"),
+    (1, 3, 1, 128, 129, 12, 2, "bf16"), (2, 8, 1, 128, 300, 10, 1, "bf16"),
+    (1, 4, 1, 128, 2500, 40, 1, "bf16"), (1, 8, 1, 64, 700, 24, 1, "bf16"),
+    (1, 2, 1, 64, 257, 4, 1, "f32")])
+@pytest.mark.parametrize("p,alpha", [(2.0, 2.0), (3.0, 1.0)])
+def test_position_launch_shapes(torch, cb, orc, shape, p, alpha):   # noqa: F811
+    L, Hq, Hkv, D, T, m, S, dt = shape
+    w = W.custom(layers=L, q_heads=Hq, kv_heads=Hkv, head_dim=D, q_len=m, seq_len=T, senders=S,
+                 dtype=dt, cfg_id=412)
+    say(f"case {shape} p={p}")
+    q = W.gen_q(w)
+    K, _ = W.gen_kv(w, want_v=False)
+    check_position(orc, w, q, K, run_position(torch, cb, w, q, K, p, alpha), p, alpha, str(shape))
