@@ -1,12 +1,13 @@
-// Per-unit top-k kernels (gfx950) running the radix select of
+// Per-unit top-k kernels (gfx950) running the selections of
 // select_impl.h, one workgroup per unit.
 //
-// Rows of up to 65536 scores are read once into registers, four scores per
+// Rows of up to 32768 scores are read once into registers, four scores per
 // 16-byte vector and KV vectors per thread (select_unit_vec), in the
 // workgroup size measured fastest for each length on MI355X: 512 threads
 // with KV = 1 or 2 up to 4096 scores, 1024 with KV = 2 up to 8192, 512 with
 // KV = 8 up to 16384 (four workgroups fit a compute unit), 1024 with KV = 8
-// or 16 up to 65536.  Longer rows re-read the
+// up to 32768.  Rows of up to 524288 scores are read twice, with fine bins of
+// a sampled range in LDS (select_unit_bins).  Longer rows re-read the
 // scores from L2 on every digit pass; when there are fewer units than
 // compute units they run in 1024-thread workgroups (the extra threads per
 // unit are otherwise idle hardware) whose ordered passes read the row
@@ -51,6 +52,20 @@ __global__ __launch_bounds__(NT) void select_vec_kernel(const float* __restrict_
     return;
   }
   select_unit_vec<NT, KV>(importance + (size_t)u * T, T, keep, idx + (size_t)u * keep, work);
+}
+
+__global__ __launch_bounds__(1024, 8) void select_bins_kernel(
+    const float* __restrict__ importance, int64_t T64, int64_t keep64, int32_t* __restrict__ idx,
+    const uint32_t* __restrict__ err) {
+  extern __shared__ __align__(16) uint32_t hist[];
+  const int T = (int)T64;
+  const int keep = (int)keep64;
+  const int u = blockIdx.x;
+  if (err && *err != 0u) {   // the scores are not valid: no selection
+    for (int i = threadIdx.x; i < keep; i += 1024) idx[(size_t)u * keep + i] = -1;
+    return;
+  }
+  select_unit_bins<1024>(importance + (size_t)u * T, T, keep, idx + (size_t)u * keep, hist);
 }
 
 // One part of a split row per workgroup: unit blockIdx.x / parts, part
@@ -208,11 +223,15 @@ hipError_t launch_select(const float* importance, int64_t units, int64_t T, int6
     select_vec_kernel<512, 8><<<g, 512, 0, s>>>(importance, T, keep, idx, err);
   } else if (T <= 4 * 8 * 1024) {
     select_vec_kernel<1024, 8><<<g, 1024, 0, s>>>(importance, T, keep, idx, err);
-  } else if (T <= 4 * 16 * 1024) {
-    select_vec_kernel<1024, 16><<<g, 1024, 0, s>>>(importance, T, keep, idx, err);
+  } else if (T <= kBinsMaxT) {
+    // Longer rows do not fit the registers of half a compute unit.  288 units:
+    // 65536 scores 86 us in registers (one workgroup a compute unit, two
+    // rounds), 61 us here; 100003 scores 504 us with every pass over L2, 86 us
+    // here.  Below the line registers win: 864 x 16384 38 against 50 us.
+    const size_t lds = (size_t)select_bins_words(T) * 4;
+    select_bins_kernel<<<g, 1024, lds, s>>>(importance, T, keep, idx, err);
   } else if (units < compute_units()) {
-    // T > 65536: ceil(T / 1024) > 64 keys per thread; the ordered passes
-    // stage chunks of the row in LDS.
+    // the ordered passes stage chunks of the row in LDS
     const size_t lds = (size_t)select_stage_words(kLongChunk) * 4;
     select_kernel<1024, true><<<g, 1024, lds, s>>>(importance, T, keep, idx, err);
   } else {

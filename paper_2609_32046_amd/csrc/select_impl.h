@@ -18,10 +18,9 @@
 namespace cb {
 
 __device__ __forceinline__ uint32_t order_key(float f) {
-  uint32_t b = __float_as_uint(f);
-  if ((b & 0x7f800000u) == 0x7f800000u && (b & 0x007fffffu)) return 0u;   // NaN
-  if (b == 0x80000000u) b = 0u;                                            // -0 == +0
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+  const uint32_t b = __float_as_uint(f + 0.f);   // -0 + 0 == +0
+  const uint32_t k = b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
+  return f != f ? 0u : k;   // NaN
 }
 
 // LDS a select_unit<NT> call needs besides the keys, in uint32 words.
@@ -690,6 +689,260 @@ __device__ __forceinline__ void select_unit_vec(const float* __restrict__ row, i
         eb += q[e];
       }
     }
+  }
+}
+
+// Rows too long to hold in registers, up to kBinsMaxT scores, in one
+// workgroup of NT threads and two reads of the row as a rule:
+//
+//   1. A sample (one score per thread) gives a key range; the first read
+//      counts every key in kBins equal bins of that range (one more bin on each
+//      side), and the bin holding the keep-th largest key becomes the new
+//      range.  Keys are the scores' bit patterns, so the bins are as fine as
+//      the scores are close: of 100003 log-normal scores the bin holds about 50.
+//      While it holds more than kBinsCap keys and spans more than one, the row
+//      is read again with the bins cut from that range (heavy ties, a
+//      threshold outside the sample).
+//   2. The last read marks in an LDS bit mask every key above the range, and
+//      lists the keys inside it, or marks them too when the range is one key.
+//   3. The listed keys are ranked against one another by (key descending,
+//      position ascending), or the marked ties taken in position order, and
+//      the mask is written out: each wave turns 64 positions into slots.
+//
+// Bound by instruction issue (about a dozen a key and read): 288 x 100003 scores
+// take 86 us, 1.3 TB/s of the row read once, where the radix passes over L2
+// took 504 us; one row alone 45 us.
+// Loads are dwords, coalesced (any alignment), the next kLoads of a thread in
+// flight while the last ones are worked on.
+constexpr int kBins = 8192;          // the first and last lie outside the range
+constexpr int kBinsCap = 512;
+constexpr int64_t kBinsMaxT = 524288;
+// LDS words: the histogram, later the two masks of ceil(T/64) 64-bit words.
+__host__ __device__ constexpr int64_t select_bins_words(int64_t T) {
+  const int64_t mask = 4 * ((T + 63) / 64);
+  return mask > kBins ? mask : kBins;
+}
+
+template <int NT>
+__device__ __forceinline__ void select_unit_bins(const float* __restrict__ row, int T, int keep,
+                                                 int32_t* __restrict__ out, uint32_t* hist) {
+  constexpr int kLoads = 8;
+  constexpr int kWaves = NT / 64;
+  constexpr int kOwn = kBins / NT;
+  static_assert(kOwn % 4 == 0 && kOwn <= 32, "bins per thread");
+  __shared__ uint32_t scratch[kWaves + 1];
+  __shared__ uint32_t red[2][kWaves];
+  __shared__ uint32_t s_bin, s_need, s_count, s_list;
+  __shared__ uint32_t c_key[kBinsCap], c_pos[kBinsCap];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+
+  // Every key of the row, in position order (batch, load, wave, lane).  The
+  // body gets (key, valid, load j of the batch); after(b0) ends a batch.
+  auto each = [&](auto&& body, auto&& after) {
+    float next[kLoads], raw[kLoads];
+    auto load = [&](int b0) {
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) {
+        const int p = b0 + j * NT + tid;
+        next[j] = row[p < T ? p : T - 1];
+      }
+    };
+    load(0);
+    int b0 = 0;
+    for (; b0 + kLoads * NT <= T; b0 += kLoads * NT) {
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) raw[j] = next[j];
+      if (b0 + kLoads * NT < T) load(b0 + kLoads * NT);
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) body(order_key(raw[j]), true, b0, j);
+      after(b0);
+    }
+    if (b0 < T) {
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) body(order_key(next[j]), b0 + j * NT + tid < T, b0, j);
+      after(b0);
+    }
+  };
+
+  // 1. the sample's range, and whether the sample repeats its ends (ties)
+  uint32_t lo, hi;
+  bool tied;
+  {
+    const uint32_t k = order_key(row[(int)((int64_t)tid * T / NT)]);
+    lo = hi = k;
+    for (int off = 32; off > 0; off >>= 1) {
+      const uint32_t a = __shfl_xor(lo, off), b = __shfl_xor(hi, off);
+      lo = a < lo ? a : lo;
+      hi = b > hi ? b : hi;
+    }
+    if (lane == 0) {
+      red[0][wave] = lo;
+      red[1][wave] = hi;
+    }
+    __syncthreads();
+    for (int w = 0; w < kWaves; ++w) {
+      lo = red[0][w] < lo ? red[0][w] : lo;
+      hi = red[1][w] > hi ? red[1][w] : hi;
+    }
+    tied = __syncthreads_count(k == lo || k == hi) > NT / 16;
+  }
+  uint32_t need = (uint32_t)keep, count;
+  for (bool first = true;; first = false) {
+    for (int i = tid; i < kBins; i += NT) hist[i] = 0u;
+    if (tid == 0) s_list = 0u;
+    __syncthreads();
+    // Bin d holds the keys base + (d << sh) and up, bin 0 also those below
+    // base and the last bin all above it.
+    int sh = 0;
+    while (((hi - lo) >> sh) > (uint32_t)kBins - 3u) ++sh;
+    const uint32_t base = !first ? lo : lo < (1u << sh) ? 0u : lo - (1u << sh);
+    const uint32_t span = hi - lo;
+    auto digit = [&](uint32_t key) {
+      const uint32_t d = ((key > base ? key : base) - base) >> sh;
+      return d < (uint32_t)kBins - 1u ? d : (uint32_t)kBins - 1u;
+    };
+    if (first && !tied) {
+      each([&](uint32_t key, bool valid, int, int) {
+        if (valid) atomicAdd(&hist[digit(key)], 1u);
+      }, [](int) {});
+    } else {
+      // Later reads count the range's keys only (what lies outside is
+      // settled); a wave of equal digits adds once.
+      each([&](uint32_t key, bool valid, int, int) {
+        const bool in = valid && (first || key - lo <= span);
+        const uint64_t m = __ballot(in);
+        if (m == 0) return;
+        const uint32_t d = digit(key);
+        const uint32_t d0 = __builtin_amdgcn_readlane(d, __ffsll((unsigned long long)m) - 1);
+        if (__ballot(in && d == d0) == m) {
+          if (lane == 0) atomicAdd(&hist[d0], (uint32_t)__popcll(m));
+        } else if (in) {
+          atomicAdd(&hist[d], 1u);
+        }
+      }, [](int) {});
+    }
+    __syncthreads();
+    // The bin with (keys above it) < need <= (keys above it or in it): thread
+    // t owns the t-th highest kOwn bins.  Reads start at a bank of their own.
+    const uint4* mine = reinterpret_cast<const uint4*>(hist + (NT - 1 - tid) * kOwn);
+    uint32_t own = 0;
+#pragma unroll
+    for (int q = 0; q < kOwn / 4; ++q) {
+      const uint4 v = mine[(q + tid) & (kOwn / 4 - 1)];
+      own += v.x + v.y + v.z + v.w;
+    }
+    uint32_t total;
+    uint32_t above = block_exclusive_scan<NT>(own, scratch, &total);
+    if (above < need && above + own >= need) {
+      for (int q = kOwn - 1; q >= 0; --q) {
+        const uint32_t c = hist[(NT - 1 - tid) * kOwn + q];
+        if (above + c >= need) {
+          s_bin = (uint32_t)((NT - 1 - tid) * kOwn + q);
+          s_need = need - above;
+          s_count = c;
+          break;
+        }
+        above += c;
+      }
+    }
+    __syncthreads();
+    const uint32_t bin = s_bin;
+    need = s_need;
+    count = s_count;
+    // The bin's keys; the outer bins of a first read reach the ends.
+    const uint64_t b_lo = (uint64_t)base + ((uint64_t)bin << sh);
+    uint64_t b_hi = b_lo + ((1ull << sh) - 1ull);
+    const uint64_t cap = first ? 0xffffffffull : (uint64_t)hi;
+    if (bin == (uint32_t)kBins - 1u || b_hi > cap) b_hi = cap;
+    lo = bin == 0u && first ? 0u : (uint32_t)b_lo;
+    hi = (uint32_t)b_hi;
+    if (count <= (uint32_t)kBinsCap || lo == hi) break;
+    __syncthreads();   // s_bin.. are read before the next pass writes them
+  }
+
+  // 2. the masks (the histogram's words), one 64-bit word per 64 positions:
+  //    lane j gathers load j's words of a batch and stores them together
+  const bool list = count <= (uint32_t)kBinsCap;
+  const int words = (T + 63) / 64;
+  uint64_t* taken = reinterpret_cast<uint64_t*>(hist);
+  uint64_t* ties = taken + words;
+  {
+    const uint32_t span = hi - lo;
+    uint64_t g = 0, e = 0;
+    each([&](uint32_t key, bool valid, int b0, int j) {
+      const uint64_t gj = __ballot(valid && key > hi);
+      const bool in = valid && key - lo <= span;
+      if (lane == j) g = gj;
+      if (list) {
+        if (in) {
+          const uint32_t at = atomicAdd(&s_list, 1u);
+          c_key[at] = key;
+          c_pos[at] = (uint32_t)(b0 + j * NT + tid);
+        }
+      } else {
+        const uint64_t ej = __ballot(in);
+        if (lane == j) e = ej;
+      }
+    }, [&](int b0) {
+      const int w = (b0 >> 6) + lane * kWaves + wave;
+      if (lane < kLoads && w < words) {
+        taken[w] = g;
+        if (!list) ties[w] = e;
+      }
+    });
+  }
+  __syncthreads();
+
+  // 3. the keys of the range that are taken
+  const int per = (words + NT - 1) / NT;
+  const int w0 = tid * per < words ? tid * per : words;
+  const int w1 = w0 + per < words ? w0 + per : words;
+  uint32_t total;
+  if (list) {
+    for (uint32_t i = tid; i < count; i += NT) {
+      const uint32_t k = c_key[i], p = c_pos[i];
+      uint32_t rank = 0;
+      for (uint32_t j = 0; j < count; ++j) {   // the same j in every lane
+        const uint32_t kj = c_key[j];
+        rank += kj > k || (kj == k && c_pos[j] < p);
+      }
+      if (rank < need) atomicOr((unsigned long long*)&taken[p >> 6], 1ull << (p & 63u));
+    }
+    __syncthreads();
+  } else {
+    uint32_t n = 0;
+    for (int w = w0; w < w1; ++w) n += (uint32_t)__popcll(ties[w]);
+    uint32_t before = block_exclusive_scan<NT>(n, scratch, &total);
+    for (int w = w0; w < w1; ++w) {
+      uint64_t e = ties[w];
+      const uint32_t c = (uint32_t)__popcll(e);
+      if (before + c > need) {   // only the first need - before of them
+        uint64_t t = 0;
+        for (uint32_t k = before; k < need; ++k) {
+          t |= e & (0 - e);
+          e &= e - 1;
+        }
+        e = t;
+      }
+      taken[w] |= e;
+      before += c;
+    }
+    // taken[w0..w1) is this thread's own until the scan's barriers below
+  }
+  uint32_t n = 0;
+  for (int w = w0; w < w1; ++w) n += (uint32_t)__popcll(taken[w]);
+  uint32_t slot = block_exclusive_scan<NT>(n, scratch, &total);
+  uint32_t* first_slot = reinterpret_cast<uint32_t*>(ties);
+  for (int w = w0; w < w1; ++w) {
+    first_slot[w] = slot;
+    slot += (uint32_t)__popcll(taken[w]);
+  }
+  __syncthreads();
+#pragma unroll 4
+  for (int w = wave; w < words; w += kWaves) {
+    const uint64_t m = taken[w];
+    const uint32_t at = first_slot[w] + lanes_below(m);
+    if (((m >> lane) & 1ull) && at < (uint32_t)keep) out[at] = w * 64 + lane;
   }
 }
 }  // namespace cb
