@@ -19,12 +19,15 @@
  *     valid once the stream reaches that point.  No call synchronises,
  *     allocates device memory or keeps a pointer after it returns.  Calls are
  *     reentrant; calls that share a workspace must not overlap in time.
- *   - cb_score and cb_pipeline enqueue, on `stream`, a small kernel that
- *     clears the call's synchronisation words in `ws` and one persistent
+ *   - cb_score and cb_pipeline enqueue, on `stream`, either a small kernel
+ *     that clears the call's synchronisation words in `ws` and one persistent
  *     kernel whose resident workgroups take every work item of the call from
- *     a device queue (one more kernel adds row-group sums in cb_score when
- *     G*m > 512).  Their workgroups wait on one another through `ws`, with
- *     bounded waits; two calls sharing a workspace must not overlap.
+ *     a device queue, or, where that is shorter (small calls, or calls whose
+ *     items fill whole rounds of workgroups), one kernel per score pass (and
+ *     one that folds the row statistics between them).  One more kernel adds
+ *     row-group sums when G*m > 512.  The persistent kernel's workgroups wait
+ *     on one another through `ws`, with bounded waits; two calls sharing a
+ *     workspace must not overlap.
  *   - The caller owns every buffer.  Outputs must not alias inputs.
  *   - On an argument error nothing is launched and a negative CB_ERR_* code
  *     is returned.  CB_ERR_HIP reports a launch failure.
@@ -91,7 +94,8 @@ size_t cb_score_workspace_bytes(const cb_layout* lay);
  * bytes; its contents need not be initialised.  Deterministic: the same
  * inputs give bitwise-identical outputs.
  * Failure inside the kernel: workgroups of the persistent kernel wait on one
- * another with bounded waits.  A wait that gives up (it cannot in a correct
+ * another with bounded waits (a wait limit of 0 makes the second of the plain
+ * passes give up likewise).  A wait that gives up (it cannot in a correct
  * run; see cb_set_wait_limit) sets an error word in `ws`, every later wait
  * gives up at once, the affected importance and row_lse entries are NaN, and
  * every kernel still exits.  cb_score_status reports the word. */
@@ -232,8 +236,9 @@ size_t cb_position_workspace_bytes(const cb_layout* lay);
  * importance (nullable): [S][L][Hkv][T], receives cb_score's importance
  * (held in `ws` when NULL).  Computed in fp32 from bf16/fp32 inputs with
  * fp32 accumulation; sums over layers and heads in fp64.  Deterministic.
- * Enqueues the clearing kernel and the persistent score kernel (second pass
- * extended with the pooled per-token sums), then two small kernels. */
+ * Enqueues the kernels of cb_score (second pass
+ * extended with the pooled per-token sums), then one small kernel; calls too
+ * small to fill the device run each pass as a launch of its own instead. */
 int cb_position_score(const void* q, const void* k, const cb_layout* lay, double p, double alpha,
                       float* score, float* qscore, float* corr, float* importance, void* ws,
                       size_t ws_bytes, void* stream);

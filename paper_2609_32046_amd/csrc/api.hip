@@ -116,22 +116,19 @@ int prepare_score(const void* q, const void* k, const cb_layout* lay, float* imp
 
 // Workspace of cb_position_score: the score kernel's, then the per-unit
 // numerator terms, then (when the caller passes no importance buffer) the
-// importance, then the fp64 per-position layer sums and corrections.
+// importance.
 struct PositionWs {
   cb::ScorePlan plan;
-  size_t off_numer, off_importance, off_qpre, off_corr, total;
+  size_t off_numer, off_importance, total;
 };
 
 bool position_ws(const cb_layout* lay, PositionWs* pw) {
   if (check_layout(lay) != CB_OK || !plan_for(lay, &pw->plan, true)) return false;
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t ut = (size_t)pw->plan.units * (size_t)pw->plan.T;
-  const size_t st = (size_t)pw->plan.S * (size_t)pw->plan.T;
   size_t off = al(pw->plan.total_bytes);
   pw->off_numer = off; off = al(off + ut * sizeof(float));
   pw->off_importance = off; off = al(off + ut * sizeof(float));
-  pw->off_qpre = off; off = al(off + st * sizeof(double));
-  pw->off_corr = off; off = al(off + st * sizeof(double));
   pw->total = off;
   return true;
 }
@@ -400,8 +397,6 @@ int cb_position_score(const void* q, const void* k, const cb_layout* lay, double
   cb::PositionFinish f;
   f.importance = imp;
   f.numer = a.numer;
-  f.qpre = reinterpret_cast<double*>(w + pw.off_qpre);
-  f.corr64 = reinterpret_cast<double*>(w + pw.off_corr);
   f.score = score;
   f.qscore = qscore;
   f.corr = corr;

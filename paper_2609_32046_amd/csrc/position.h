@@ -11,8 +11,6 @@ namespace cb {
 struct PositionFinish {
   const float* importance;   // [U][T]
   const float* numer;        // [U][T], the score kernel's numerator terms
-  double* qpre;              // [S][T] workspace
-  double* corr64;            // [S][T] workspace
   float* score;              // [S][T]
   float* qscore;             // [S][T] or null
   float* corr;               // [S][T] or null

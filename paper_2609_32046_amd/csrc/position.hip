@@ -5,8 +5,8 @@
 //                    (Q before pooling), the correction numerator (from the
 //                    score kernel's pooled per-token terms) and denominator
 //                    (Pool_7 of each unit's mean weight, raised to p), then
-//                    C_{p,t}; fp64 accumulation.
-//   position_output  Q_t = Pool_7 of the layer sum, S_t = Q_t * C_t^alpha.
+//                    C_{p,t}; fp64 accumulation; then Q_t = Pool_7 of the
+//                    layer sum and S_t = Q_t * C_t^alpha.
 //   spans_kernel     the span rule, one workgroup per sender.
 //   gather_rows      continuous rows at the selected positions.
 //
@@ -22,34 +22,48 @@ namespace cb {
 namespace {
 
 constexpr int kPool = 3;          // Pool_7: positions t-3 .. t+3
-constexpr int kTermWaves = 8;     // waves sharing one block of positions
-constexpr int kTermLanes = 64;    // positions per block
+constexpr int kTermWaves = 16;    // waves sharing one block of positions
+constexpr int kTermLanes = 64;    // positions per block, the outer 3 on each side
+constexpr int kTermOut = kTermLanes - 2 * kPool;   // for its pooling only
 constexpr int kTermBatch = 4;     // units whose loads are in flight together
 
 struct TermArgs {
   const float* importance;   // [U][T]
   const float* numer;        // [U][T]
-  double* qpre;              // [S][T]
-  double* corr;              // [S][T]
+  float* score;              // [S][T]
+  float* qscore;             // [S][T] or null
+  float* corr;               // [S][T] or null
   int64_t T;
   int LH;                    // units per sender
-  int pow_mode;
-  double p, inv_mG, num_scale, q_scale;
+  int n;                     // p (kTermInteger)
+  double p, alpha, inv_mG, num_scale, q_scale;
 };
 
-// Block: 8 waves x 64 positions; wave w takes the sender's units w, w+8, ...
+// Powers of the terms: the PowModes, and whole powers above 2 by products
+// (3 x 288 units x 3001 positions at p = 3: 41 us with pow()).
+enum TermPow : int { kTermSquare, kTermInteger, kTermGeneral, kTermMax };
+
+// Out of line: four copies of it in the unit batch spill.
+__device__ __noinline__ double pow_call(double x, double p) { return pow(x, p); }
+
+// Block: 16 waves x 64 positions; wave w takes the sender's units w, w+16, ...
+// Bound by the latency of the loads, so that eight waves a block (15 us at 288
+// units x 8192 positions, the output in a launch of its own 5 us more) gave way
+// to sixteen.
+template <int MODE>
 __global__ __launch_bounds__(kTermWaves * kTermLanes) void position_terms(TermArgs a) {
   __shared__ double part[3][kTermWaves][kTermLanes];
+  __shared__ double qpre[kTermLanes];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int s = blockIdx.y;
-  const int64_t t = (int64_t)blockIdx.x * kTermLanes + lane;
-  const bool in = t < a.T;
+  const int64_t t = (int64_t)blockIdx.x * kTermOut - kPool + lane;
+  const bool in = t >= 0 && t < a.T;
   const int64_t lo = t - kPool < 0 ? 0 : t - kPool;
   const int64_t hi = t + kPool < a.T - 1 ? t + kPool : a.T - 1;
   double q = 0.0, num = 0.0, den = 0.0;
   if (in) {
-    // Units wave, wave + 8, ... in that order; the loads of kTermBatch units
-    // are issued before any of them is used (the loop is latency-bound).
+    // Units wave, wave + 16, ... in that order; the loads of kTermBatch units
+    // are issued before any of them is used.
     // The window's 7 loads are clamped into [lo, hi], which repeats an end
     // value near the sequence ends and leaves the maximum unchanged.
     for (int j0 = wave; j0 < a.LH; j0 += kTermBatch * kTermWaves) {
@@ -75,12 +89,16 @@ __global__ __launch_bounds__(kTermWaves * kTermLanes) void position_terms(TermAr
         for (int d = 1; d <= 2 * kPool; ++d) pooled = fmaxf(pooled, win[b][d]);
         const double x = (double)pooled * a.inv_mG;   // Pool_7 of the unit's token mean
         q += (double)win[b][kPool];
-        if (a.pow_mode == kPowMax) {
+        if constexpr (MODE == kTermMax) {
           num = fmax(num, (double)nu[b]);
           den = fmax(den, x);
         } else {
           num += (double)nu[b];
-          den += a.pow_mode == kPowSquare ? x * x : pow(x, a.p);
+          double xp = x * x;
+          if constexpr (MODE == kTermInteger)
+            for (int i = 2; i < a.n; ++i) xp *= x;
+          if constexpr (MODE == kTermGeneral) xp = pow_call(x, a.p);
+          den += xp;
         }
       }
     }
@@ -89,11 +107,11 @@ __global__ __launch_bounds__(kTermWaves * kTermLanes) void position_terms(TermAr
   part[1][wave][lane] = num;
   part[2][wave][lane] = den;
   __syncthreads();
-  if (wave != 0 || !in) return;
+  if (wave != 0) return;
   q = num = den = 0.0;
   for (int w = 0; w < kTermWaves; ++w) {
     q += part[0][w][lane];
-    if (a.pow_mode == kPowMax) {
+    if (MODE == kTermMax) {
       num = fmax(num, part[1][w][lane]);
       den = fmax(den, part[2][w][lane]);
     } else {
@@ -105,9 +123,7 @@ __global__ __launch_bounds__(kTermWaves * kTermLanes) void position_terms(TermAr
   double c;
   if (num == 0.0 && den == 0.0) {
     c = 1.0;
-  } else if (a.pow_mode == kPowMax) {
-    c = num / den;
-  } else if (a.pow_mode == kPowSquare) {
+  } else if (MODE == kTermMax || MODE == kTermSquare) {
     c = num / den;
   } else {
     c = pow(num / den, 1.0 / (a.p - 1.0));
@@ -116,26 +132,17 @@ __global__ __launch_bounds__(kTermWaves * kTermLanes) void position_terms(TermAr
   // mean); fp32 underflow of the smallest per-token terms can only lower
   // the numerator, so the bound is restored here.
   if (!(c >= 1.0)) c = 1.0;
-  a.qpre[(size_t)s * a.T + t] = q * a.q_scale;
-  a.corr[(size_t)s * a.T + t] = c;
-}
-
-__global__ void position_output(const double* __restrict__ qpre, const double* __restrict__ corr,
-                                int64_t T, int64_t n, double alpha, float* __restrict__ score,
-                                float* __restrict__ qscore, float* __restrict__ corr_out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int64_t s = i / T, t = i - s * T;
-  const int64_t lo = t - kPool < 0 ? 0 : t - kPool;
-  const int64_t hi = t + kPool < T - 1 ? t + kPool : T - 1;
-  const double* row = qpre + s * T;
-  double qv = row[lo];
-  for (int64_t d = lo + 1; d <= hi; ++d) qv = fmax(qv, row[d]);
-  const double c = corr[i];
-  const double w = alpha == 0.0 ? 1.0 : alpha == 2.0 ? c * c : pow(c, alpha);
-  score[i] = (float)(qv * w);
-  if (qscore) qscore[i] = (float)qv;
-  if (corr_out) corr_out[i] = (float)c;
+  // Q_t = Pool_7 of the layer sums (this wave's own LDS writes), S_t = Q_t C^alpha
+  qpre[lane] = q * a.q_scale;
+  __builtin_amdgcn_wave_barrier();
+  if (!in || lane < kPool || lane >= kTermLanes - kPool) return;
+  double qv = qpre[lane + (int)(lo - t)];
+  for (int64_t d = lo + 1; d <= hi; ++d) qv = fmax(qv, qpre[lane + (int)(d - t)]);
+  const double w = a.alpha == 0.0 ? 1.0 : a.alpha == 2.0 ? c * c : pow(c, a.alpha);
+  const size_t i = (size_t)s * a.T + t;
+  a.score[i] = (float)(qv * w);
+  if (a.qscore) a.qscore[i] = (float)qv;
+  if (a.corr) a.corr[i] = (float)c;
 }
 
 // ---- span rule ----------------------------------------------------------------
@@ -486,22 +493,27 @@ hipError_t launch_position_finish(const PositionFinish& f, hipStream_t s) {
   TermArgs a;
   a.importance = f.importance;
   a.numer = f.numer;
-  a.qpre = f.qpre;
-  a.corr = f.corr64;
+  a.score = f.score;
+  a.qscore = f.qscore;
+  a.corr = f.corr;
   a.T = f.T;
   a.LH = f.LH;
-  a.pow_mode = f.pow_mode;
+  a.n = (int)(f.pow_mode == kPowGeneral ? f.p : 2.0);
   a.p = f.p;
+  a.alpha = f.alpha;
   a.inv_mG = 1.0 / ((double)f.m * f.G);
   a.num_scale = f.num_scale;
   a.q_scale = 1.0 / ((double)f.m * f.Hq);
-  const dim3 grid((unsigned)((f.T + kTermLanes - 1) / kTermLanes), (unsigned)f.S);
-  position_terms<<<grid, kTermWaves * kTermLanes, 0, s>>>(a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t n = (int64_t)f.S * f.T;
-  position_output<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(f.qpre, f.corr64, f.T, n, f.alpha,
-                                                              f.score, f.qscore, f.corr);
+  const dim3 grid((unsigned)((f.T + kTermOut - 1) / kTermOut), (unsigned)f.S);
+  const int threads = kTermWaves * kTermLanes;
+  if (f.pow_mode == kPowMax)
+    position_terms<kTermMax><<<grid, threads, 0, s>>>(a);
+  else if (f.pow_mode == kPowSquare)
+    position_terms<kTermSquare><<<grid, threads, 0, s>>>(a);
+  else if (f.p == (double)a.n && a.n > 2)
+    position_terms<kTermInteger><<<grid, threads, 0, s>>>(a);
+  else
+    position_terms<kTermGeneral><<<grid, threads, 0, s>>>(a);
   return hipGetLastError();
 }
 

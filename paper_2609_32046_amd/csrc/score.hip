@@ -80,10 +80,10 @@ bool make_score_plan(int L, int Hq, int Hkv, int D, int m, int S, int64_t T, int
   // as much as real ones: 36 x 8 units of 160 rows (three blocks in four waves
   // instead of four) 630 -> 493 us as a whole position-level call.
   static constexpr int kShapes[][2] = {{1, 1}, {1, 2}, {1, 3}, {1, 4}, {2, 3}, {2, 4}, {4, 3},
-                                       {4, 4}, {4, 5}, {8, 4}};
+                                       {4, 4}, {4, 5}, {4, 6}, {4, 8}, {8, 4}};
   p->row_groups = (p->Rp + kRowsPerGroup - 1) / kRowsPerGroup;
   for (const auto& sh : kShapes) {
-    if ((dtype == 0 && sh[1] == 3) || (position && sh[1] == 5)) continue;
+    if ((dtype == 0 && (sh[1] == 3 || sh[1] > 5)) || (position && sh[1] > 4)) continue;
     p->waves = sh[0];
     p->rb = sh[1];
     if (16 * sh[0] * sh[1] >= p->Rp) break;

@@ -61,6 +61,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 
@@ -79,59 +80,78 @@ template <int ESZ, int D, int TT>
 struct Geo {
   static constexpr int kRowBytes = D * ESZ;
   static constexpr int kChunks = kRowBytes / 16;          // 16-byte chunks per K row
-  static constexpr int kSegs = kChunks / 4;               // chunks per lane group
-  static constexpr int kSwz = kChunks >= 16 ? 15 : kChunks - 1;
   static constexpr int kTileBytes = TT * kRowBytes;
   static constexpr int kTileChunks = TT * kChunks;
-  static constexpr int kBlocks = TT / 16;                 // 16-position column blocks per tile
 };
 
 // K-tile slot layout: thread `tid` of an NT-thread workgroup owns slots
 // j*NT + tid, j < per, of a tile of rows of `chunks` 16-byte chunks stored
-// swizzled (chunk c of row r at position c ^ (r & swz)).  When NT rows of
-// chunks span a multiple of swz+1 whole rows, slot j of a thread is its slot
-// 0 moved down j*NT/chunks rows: one per-lane offset serves every load of a
-// tile.  Checked exhaustively at compile time where it is used.
+// swizzled.  When NT chunks span a multiple of the swizzle's period in whole
+// rows, slot j of a thread is its slot 0 moved down j*NT/chunks rows: one
+// per-lane offset serves every load of a tile.  Checked exhaustively at
+// compile time where it is used.
 struct SlotGeo {
   int row, off;
 };
-constexpr SlotGeo slot_geo(int slot, int chunks, int swz, int row_bytes) {
+// Chunk c of row r is stored at c ^ swz_of(r): 16 consecutive rows then hold
+// a chunk in 16 different 16-byte bank groups of the 256-byte bank row (two
+// rows of 128 bytes share one).
+__host__ __device__ constexpr int swz_of(int row, int chunks) {
+  return chunks >= 16 ? row & 15 : (row >> 1) & 7;
+}
+constexpr SlotGeo slot_geo(int slot, int chunks, int row_bytes) {
   const int r = slot / chunks;
-  const int c = (slot % chunks) ^ (r & swz);
+  const int c = (slot % chunks) ^ swz_of(r, chunks);
   return SlotGeo{r, r * row_bytes + c * 16};
 }
-constexpr bool slots_linear(int nt, int per, int chunks, int swz, int row_bytes) {
-  if (nt % chunks != 0 || ((nt / chunks) & swz) != 0) return false;
+constexpr bool slots_linear(int nt, int per, int chunks, int row_bytes) {
+  if (nt % chunks != 0) return false;
   for (int tid = 0; tid < nt; ++tid)
     for (int j = 0; j < per; ++j) {
-      const SlotGeo g0 = slot_geo(tid, chunks, swz, row_bytes);
-      const SlotGeo gj = slot_geo(j * nt + tid, chunks, swz, row_bytes);
+      const SlotGeo g0 = slot_geo(tid, chunks, row_bytes);
+      const SlotGeo gj = slot_geo(j * nt + tid, chunks, row_bytes);
       if (gj.row != g0.row + j * (nt / chunks) || gj.off != g0.off + j * (nt / chunks) * row_bytes)
         return false;
     }
   return true;
 }
 
-__device__ __forceinline__ int swz_offset(int row, int c, int row_bytes, int swz) {
-  return row * row_bytes + ((c ^ (row & swz)) << 4);
+__device__ __forceinline__ int swz_offset(int row, int c, int row_bytes) {
+  return row * row_bytes + ((c ^ swz_of(row, row_bytes / 16)) << 4);
 }
 
-// One 16-byte segment of the contraction for a 16x16 output block.
-template <int ESZ>
-__device__ __forceinline__ void mfma_seg(const u32x4& a, const u32x4& b, f32x4& acc);
+// MFMA output blocks of M x M.  The lanes form 64/M groups; lane (lg, lc) of
+// an operand holds row lc's contiguous share lg of the contraction, and of the
+// output column lc, rows row(i, lg) in its registers i.
+template <int M> struct Mma;
+template <> struct Mma<16> {
+  typedef f32x4 Acc;
+  static constexpr int kRegs = 4, kGroups = 4;
+  __device__ static constexpr int row(int i, int lg) { return 4 * lg + i; }
+};
+template <> struct Mma<32> {
+  typedef f32x16 Acc;
+  static constexpr int kRegs = 16, kGroups = 2;
+  __device__ static constexpr int row(int i, int lg) { return (i & 3) + 8 * (i >> 2) + 4 * lg; }
+};
 
-template <>
-__device__ __forceinline__ void mfma_seg<2>(const u32x4& a, const u32x4& b, f32x4& acc) {
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-}
-
-template <>
-__device__ __forceinline__ void mfma_seg<4>(const u32x4& a, const u32x4& b, f32x4& acc) {
+// One 16-byte segment of the contraction for an output block.
+template <int ESZ, int M>
+__device__ __forceinline__ void mfma_seg(const u32x4& a, const u32x4& b,
+                                         typename Mma<M>::Acc& acc) {
+  if constexpr (ESZ == 2 && M == 32) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                  __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+  } else if constexpr (ESZ == 2) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                  __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+  } else {
+    static_assert(M == 16, "fp32 blocks are 16 x 16");
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]),
-                                               acc, 0, 0, 0);
+    for (int e = 0; e < 4; ++e)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]),
+                                                 acc, 0, 0, 0);
+  }
 }
 
 // LDS ring depth: as many K tiles as fit the workgroup's share of the
@@ -222,29 +242,16 @@ __device__ __forceinline__ float sum_lane_groups(float v) {
   return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
-// Sum / max over the 16 lanes of a DPP row (lanes 16j..16j+15: the 16 token
-// columns of one query row in the MFMA output), returned in every one of
-// them.  Two quad permutes, a half-row mirror and a row mirror, each fused
-// into the VALU op; the combination order is the same in every lane, so all
-// 16 hold bitwise-equal results.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
-                                                               0xf, 0xf, false));
+// Sum / maximum over the two lane halves l, l^32, in both.
+__device__ __forceinline__ float sum_lane_halves(float v) {
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v),
+                                                  false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
-__device__ __forceinline__ float row16_sum(float v) {
-  v += dpp_f32<0xB1>(v);    // quad_perm [1,0,3,2]
-  v += dpp_f32<0x4E>(v);    // quad_perm [2,3,0,1]
-  v += dpp_f32<0x141>(v);   // row_half_mirror
-  v += dpp_f32<0x140>(v);   // row_mirror
-  return v;
-}
-__device__ __forceinline__ float row16_max(float v) {
-  v = fmaxf(v, dpp_f32<0xB1>(v));
-  v = fmaxf(v, dpp_f32<0x4E>(v));
-  v = fmaxf(v, dpp_f32<0x141>(v));
-  v = fmaxf(v, dpp_f32<0x140>(v));
-  return v;
+__device__ __forceinline__ float max_lane_halves(float v) {
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v),
+                                                  false, false);
+  return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
 
 // Maximum over the four lane groups (see sum_lane_groups).
@@ -425,16 +432,31 @@ __device__ __forceinline__ bool real_row(const PersistArgs& a, int rho, int* qro
 // PM (position variant): 0 reads the power mode and head grouping from the
 // arguments; 1 fixes p = 2 and groups of four query heads at compile time,
 // so the per-block pooling epilogue has no run-time branches.
+// 32 x 32 blocks wherever a wave's bf16 rows allow, 16 x 16 for odd counts of
+// 16 rows, fp32, and the pooling pass (whose windows run across the 16 lanes
+// of a DPP row).  A 32 x 32 block takes half the MFMA issue slots and half the
+// operand reads per logit.
+template <int ESZ, int RB, bool POOL>
+struct BlockDim {
+  static constexpr int value = (ESZ == 2 && RB % 2 == 0 && !POOL) ? 32 : 16;
+};
+
 template <int ESZ, int D, int W, int RB, bool PASS2, bool POS, int PM = 0, bool STATIC = false>
 __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
                                            Shared<ESZ, D, W, POS, RB>& sh) {
+  constexpr int M = BlockDim<ESZ, RB, PASS2 && POS>::value;
+  using Mm = Mma<M>;
+  using Acc = typename Mm::Acc;
+  constexpr int kRegs = Mm::kRegs;
+  constexpr int NB = 16 * RB / M;                // M-row blocks per wave
   const int pow_mode = PM == 1 ? (int)kPowSquare : a.pow_mode;
   const int gshift = PM == 1 ? 2 : a.gshift;
   constexpr int kRPW = 16 * RB;                  // query rows per wave
-  constexpr int kGroupRows = kRPW * kMaxWaves;   // rows per row group
+  constexpr int kGroupRows = kRowsPerGroup;
   constexpr int TT = TileTokens<ESZ, D, W>::value;   // positions per K tile
   using Gm = Geo<ESZ, D, TT>;
-  constexpr int kBlocks = Gm::kBlocks;
+  constexpr int kBlocks = TT / M;                // M-position column blocks per tile
+  constexpr int kSegs = Gm::kChunks / Mm::kGroups;   // 16-byte chunks per lane group
   constexpr int kPer = Gm::kTileChunks / (W * 64);   // 16-byte loads per thread per tile
   constexpr int kStages = Stages<ESZ, D, W, POS, RB>::value;  // K tiles resident/in flight in LDS
   static_assert(Gm::kTileChunks % (W * 64) == 0, "tile must split evenly");
@@ -456,8 +478,8 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   asm volatile("" : "+v"(tid));
   const int wave = tid >> 6;
   const int lane = tid & 63;
-  const int lg = lane >> 4;   // lane group: which quarter of the contraction / which 4 rows
-  const int lc = lane & 15;   // lane column: token within a 16-token block / Q row
+  const int lg = lane / M;          // lane group: which share of the contraction
+  const int lc = lane & (M - 1);    // lane column: position within a block / query row
 
   const unsigned char* qb = static_cast<const unsigned char*>(a.q) +
                             (size_t)((layer * a.Hq + kvh * a.G) * a.m) * Gm::kRowBytes;
@@ -466,6 +488,77 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
 
   const int wrow0 = rg * kGroupRows + wave * kRPW;
   const bool wave_active = wrow0 < a.Rp;
+
+  const int64_t t_begin = (int64_t)chunk * a.chunk_tokens;
+  const int64_t t_end = (t_begin + a.chunk_tokens < a.T) ? t_begin + a.chunk_tokens : a.T;
+  const int ntiles = (int)((t_end - t_begin + TT - 1) / TT);
+
+  int64_t next = 0;
+
+  // ---- K tiles: direct global -> LDS loads into a kStages-deep ring -----------
+  // Lane `tid` owns LDS slot j*(W*64) + tid of a tile and fetches the K chunk
+  // whose swizzled position that slot is: every load instruction of a wave
+  // writes one contiguous KiB of LDS, and the swizzle stays the one the
+  // B-fragment reads expect.  Rows past the chunk end are clamped to its last
+  // row (always valid memory); their logits are masked or never stored.
+  int koff[kPer];   // byte offset of this lane's chunk inside a tile's rows
+  int krow[kPer];   // its row inside the tile
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int slot = j * (W * 64) + tid;
+    krow[j] = slot / Gm::kChunks;
+    const int c = (slot % Gm::kChunks) ^ swz_of(krow[j], Gm::kChunks);
+    koff[j] = krow[j] * Gm::kRowBytes + c * 16;
+  }
+  const uint32_t lds_ring = lds_offset(&ktile[0][0]) + wave * 64 * 16;
+  // Where every load of a tile shares the lane's offset, the full-tile loads
+  // take a scalar base per load and one offset register (no per-load
+  // 64-bit addresses to keep live across the tile loop).
+  constexpr bool kLinear = slots_linear(W * 64, kPer, Gm::kChunks, Gm::kRowBytes);
+  constexpr int kJBytes = (W * 64 / Gm::kChunks) * Gm::kRowBytes;
+  auto issue_tile = [&](int tile, int buf) {
+    const int64_t tbase = t_begin + (int64_t)tile * TT;
+    const unsigned char* src = kb + (size_t)tbase * Gm::kRowBytes;
+    const uint32_t dst = lds_ring + buf * Gm::kTileBytes;
+    if (kLinear && tbase + TT <= t_end) {
+      const unsigned char* ssrc = uniform_ptr(src);
+#pragma unroll
+      for (int j = 0; j < kPer; ++j)
+        load_lds16_s(ssrc + (size_t)j * kJBytes, (uint32_t)koff[0],
+                     __builtin_amdgcn_readfirstlane(dst + j * (W * 64) * 16));
+    } else if (tbase + TT <= t_end) {
+#pragma unroll
+      for (int j = 0; j < kPer; ++j)
+        load_lds16(src + koff[j], __builtin_amdgcn_readfirstlane(dst + j * (W * 64) * 16));
+    } else {
+      const int last = (int)(t_end - 1 - tbase);
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        const int over = krow[j] > last ? (krow[j] - last) * Gm::kRowBytes : 0;
+        load_lds16(src + koff[j] - over, __builtin_amdgcn_readfirstlane(dst + j * (W * 64) * 16));
+      }
+    }
+  };
+
+  // The first K tiles are requested before anything else of the item, and the
+  // query rows next, so that their latencies overlap each other's and the
+  // wait for the statistics; not in the pooling pass, whose halo blocks would
+  // wait for the tiles (864 units x 3001 positions: 502 against 515 us).
+  constexpr bool kFirst = !(PASS2 && POS);
+  if (kFirst)
+    for (int j = 0; j < kStages - 1 && j < ntiles; ++j) issue_tile(j, j);
+
+  // ---- query rows of this wave, resident in registers -----------------------
+  u32x4 qf[NB][kSegs];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    int qrow;
+    const bool real = real_row<POS>(a, wrow0 + nb * M + lc, &qrow);
+    const u32x4* src = reinterpret_cast<const u32x4*>(qb + (size_t)(real ? qrow : 0) *
+                                                              Gm::kRowBytes) + lg * kSegs;
+#pragma unroll
+    for (int sg = 0; sg < kSegs; ++sg) qf[nb][sg] = real ? src[sg] : u32x4{0, 0, 0, 0};
+  }
 
   // ---- P2 prologue: wait for the row group's statistics, fold them --------
   // One thread per row (some take two with five row blocks per wave); chunks
@@ -488,14 +581,17 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
                     a.sync + kSyncError, a.spin_limit, &sh.ok);
     }
     const int row_base = rg * kGroupRows;
-    const int nrows = (a.Rp - row_base < W * kRPW) ? a.Rp - row_base : W * kRPW;
-    for (int lr = tid; lr < nrows; lr += W * 64) {
+    for (int lr = tid; lr < W * kRPW; lr += W * 64) {
       const int row = row_base + lr;
+      int qrow;
+      if (!real_row<POS>(a, row, &qrow)) {   // padding: no weight
+        lse_lds[lr] = INFINITY;
+        continue;
+      }
       if (STATIC && a.lse2) {
         const float l2 = ok ? a.lse2[(size_t)u * a.Rp + row] : __builtin_nanf("");
         lse_lds[lr] = l2;
-        int qrow;
-        if (chunk == 0 && a.row_lse && real_row<POS>(a, row, &qrow))
+        if (chunk == 0 && a.row_lse)
           a.row_lse[(size_t)u * a.R + qrow] = l2 * 0.69314718055994530942f;
         continue;
       }
@@ -515,42 +611,25 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       }
       const float l2 = ok ? m + __log2f(z) : __builtin_nanf("");
       lse_lds[lr] = l2;
-      int qrow;
-      if (chunk == 0 && a.row_lse && real_row<POS>(a, row, &qrow))
+      if (chunk == 0 && a.row_lse)
         a.row_lse[(size_t)u * a.R + qrow] = l2 * 0.69314718055994530942f;
     }
   }
-  // ---- query rows of this wave, resident in registers -----------------------
-  u32x4 qf[RB][Gm::kSegs];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    int qrow;
-    const bool real = real_row<POS>(a, wrow0 + rb * 16 + lc, &qrow);
-    const u32x4* src = reinterpret_cast<const u32x4*>(qb + (size_t)(real ? qrow : 0) *
-                                                              Gm::kRowBytes) + lg * Gm::kSegs;
-#pragma unroll
-    for (int sg = 0; sg < Gm::kSegs; ++sg) qf[rb][sg] = real ? src[sg] : u32x4{0, 0, 0, 0};
-  }
-
   // ---- per-lane row state -----------------------------------------------------
-  // Rows held by this lane: wrow0 + rb*16 + 4*lg + i.
-  float st_m[RB][4], st_z[RB][4];   // pass 1: reference max / sum (log2 units)
-  bool per_lane_max = false;      // pass 1: a slow-path tile made the row maxima per lane
-  float row_l2[RB][4];             // pass 2: lse2 of the row (+inf for padding rows)
+  // P1 multiplies K by Q, so that a lane holds one query row a block (column
+  // wrow0 + nb*M + lc) against kRegs positions and its (max, sum) are two
+  // registers; P2 multiplies Q by K, so that a lane holds one position against
+  // rows wrow0 + nb*M + row(i, lg) and adds them in registers.
+  float st_m[NB], st_z[NB];       // pass 1: reference max / sum (log2 units)
+  // pass 2: lse2 of the row (+inf for padding rows), in registers where they
+  // fit beside the query rows, else read from LDS for each block
+  constexpr bool kL2Regs = NB <= 2 || M == 16;
+  float row_l2[kL2Regs ? NB : 1][kRegs];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      st_m[rb][i] = -INFINITY;
-      st_z[rb][i] = 0.f;
-      row_l2[rb][i] = INFINITY;
-    }
-
-  const int64_t t_begin = (int64_t)chunk * a.chunk_tokens;
-  const int64_t t_end = (t_begin + a.chunk_tokens < a.T) ? t_begin + a.chunk_tokens : a.T;
-  const int ntiles = (int)((t_end - t_begin + TT - 1) / TT);
-
-  int64_t next = 0;
+  for (int nb = 0; nb < NB; ++nb) {
+    st_m[nb] = -INFINITY;
+    st_z[nb] = 0.f;
+  }
 
   // P2 output of one tile: the sum over waves (in wave order) of the
   // per-wave column sums, as device-scope stores (the unit's SEL item reads
@@ -592,96 +671,55 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     }
   };
 
-  // ---- K tiles: direct global -> LDS loads into a kStages-deep ring -----------
-  // Lane `tid` owns LDS slot j*(W*64) + tid of a tile and fetches the K chunk
-  // whose swizzled position that slot is: every load instruction of a wave
-  // writes one contiguous KiB of LDS, and the swizzle stays the one the
-  // B-fragment reads expect.  Rows past the chunk end are clamped to its last
-  // row (always valid memory); their logits are masked or never stored.
-  int koff[kPer];   // byte offset of this lane's chunk inside a tile's rows
-  int krow[kPer];   // its row inside the tile
+  // Logits of one column block (positions tb*M .. tb*M + M-1 of the tile)
+  // against G row blocks from nb0 on.
+  auto load_block = [&](const unsigned char* kt, int tb, u32x4 (&kf)[kSegs]) {
+    const int row = tb * M + lc;
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int slot = j * (W * 64) + tid;
-    krow[j] = slot / Gm::kChunks;
-    const int c = (slot % Gm::kChunks) ^ (krow[j] & Gm::kSwz);
-    koff[j] = krow[j] * Gm::kRowBytes + c * 16;
-  }
-  const uint32_t lds_ring = lds_offset(&ktile[0][0]) + wave * 64 * 16;
-  // Where every load of a tile shares the lane's offset, the full-tile loads
-  // take a scalar base per load and one offset register (no per-load
-  // 64-bit addresses to keep live across the tile loop).
-  constexpr bool kLinear =
-      slots_linear(W * 64, kPer, Gm::kChunks, Gm::kSwz, Gm::kRowBytes);
-  constexpr int kJBytes = (W * 64 / Gm::kChunks) * Gm::kRowBytes;
-  auto issue_tile = [&](int tile, int buf) {
-    const int64_t tbase = t_begin + (int64_t)tile * TT;
-    const unsigned char* src = kb + (size_t)tbase * Gm::kRowBytes;
-    const uint32_t dst = lds_ring + buf * Gm::kTileBytes;
-    if (kLinear && tbase + TT <= t_end) {
-      const unsigned char* ssrc = uniform_ptr(src);
-#pragma unroll
-      for (int j = 0; j < kPer; ++j)
-        load_lds16_s(ssrc + (size_t)j * kJBytes, (uint32_t)koff[0],
-                     __builtin_amdgcn_readfirstlane(dst + j * (W * 64) * 16));
-    } else if (tbase + TT <= t_end) {
-#pragma unroll
-      for (int j = 0; j < kPer; ++j)
-        load_lds16(src + koff[j], __builtin_amdgcn_readfirstlane(dst + j * (W * 64) * 16));
-    } else {
-      const int last = (int)(t_end - 1 - tbase);
-#pragma unroll
-      for (int j = 0; j < kPer; ++j) {
-        const int over = krow[j] > last ? (krow[j] - last) * Gm::kRowBytes : 0;
-        load_lds16(src + koff[j] - over, __builtin_amdgcn_readfirstlane(dst + j * (W * 64) * 16));
-      }
-    }
-  };
-
-  // One 16-token column block: this wave's 64 rows against tokens
-  // tb*16..tb*16+15 of the tile, as four 16x16 MFMA blocks (one per row
-  // block) over the kSegs contraction segments.
-  auto load_block = [&](const unsigned char* kt, int tb, u32x4 (&kf)[Gm::kSegs]) {
-    const int row = tb * 16 + lc;
-#pragma unroll
-    for (int sg = 0; sg < Gm::kSegs; ++sg)
+    for (int sg = 0; sg < kSegs; ++sg)
       kf[sg] = *reinterpret_cast<const u32x4*>(
-          kt + swz_offset(row, lg * Gm::kSegs + sg, Gm::kRowBytes, Gm::kSwz));
+          kt + swz_offset(row, lg * kSegs + sg, Gm::kRowBytes));
   };
-  auto mfma_block = [&](const u32x4 (&kf)[Gm::kSegs], f32x4 (&acc)[RB]) {
+  constexpr int G = M == 16 ? NB : 1;   // row blocks per pipeline step
+  auto mfma_block = [&](const u32x4 (&kf)[kSegs], int nb0, Acc (&acc)[G]) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int g = 0; g < G; ++g) acc[g] = Acc{};
 #pragma unroll
-    for (int sg = 0; sg < Gm::kSegs; ++sg)
+    for (int sg = 0; sg < kSegs; ++sg)
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) mfma_seg<ESZ>(qf[rb][sg], kf[sg], acc[rb]);
-  };
-  auto column_block = [&](const unsigned char* kt, int tb, f32x4 (&acc)[RB]) {
-    u32x4 kf[Gm::kSegs];
-    load_block(kt, tb, kf);
-    mfma_block(kf, acc);
-  };
-  // Software pipeline over the column blocks of a tile: the LDS reads
-  // and MFMAs of block tb+1 are issued ahead of block tb's exp epilogue, and
-  // the scheduler is asked to interleave them, so the matrix unit and the
-  // VALU work at the same time within one wave.  (Not for fp32, which waits on
-  // its 32-cycle MFMAs: the hints gain nothing and cost minutes of compile
-  // time.)
-  constexpr int kMfmaPerBlock = RB * Gm::kSegs * (ESZ == 4 ? 4 : 1);
-  auto pipelined_tile = [&](const unsigned char* kt, auto&& epilogue) {
-    u32x4 kf[2][Gm::kSegs];
-    f32x4 acc[2][RB];
-    load_block(kt, 0, kf[0]);
-    mfma_block(kf[0], acc[0]);
-#pragma unroll
-    for (int tb = 0; tb < kBlocks; ++tb) {
-      const int cur = tb & 1;
-      if (tb < kBlocks - 1) {
-        load_block(kt, tb + 1, kf[cur ^ 1]);
-        mfma_block(kf[cur ^ 1], acc[cur ^ 1]);
+      for (int g = 0; g < G; ++g) {
+        if constexpr (PASS2)
+          mfma_seg<ESZ, M>(qf[nb0 + g][sg], kf[sg], acc[g]);
+        else
+          mfma_seg<ESZ, M>(kf[sg], qf[nb0 + g][sg], acc[g]);
       }
-      epilogue(tb, acc[cur]);
-      if (ESZ == 2 && tb < kBlocks - 1) interleave_mfma_valu<kMfmaPerBlock, 3>();
+  };
+  // Software pipeline over the (column block, row blocks) steps of a tile: the
+  // MFMAs of a step are issued ahead of the exp epilogue of the one before, and
+  // the scheduler is asked to interleave them, so the matrix unit and the
+  // VALU work at the same time within one wave; a column block's LDS reads
+  // are issued a step earlier still.  (No hints for fp32, which waits on
+  // its 32-cycle MFMAs: they gain nothing and cost minutes of compile time.)
+  constexpr int kSteps = kBlocks * (NB / G);
+  constexpr int kKf = NB * M <= 64 ? 2 : 1;   // K fragment sets (registers)
+  constexpr int kMfmaPerStep = G * kSegs * (ESZ == 4 ? 4 : 1);
+  constexpr int kValuPerMfma = 3 * G * kRegs / kMfmaPerStep;
+  auto pipelined_tile = [&](const unsigned char* kt, auto&& epilogue) {
+    u32x4 kf[kKf][kSegs];
+    Acc acc[2][G];
+    load_block(kt, 0, kf[0]);
+    mfma_block(kf[0], 0, acc[0]);
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+      const int tb = st / (NB / G), nb = st % (NB / G) * G;
+      if (st + 1 < kSteps) {
+        const int tn = (st + 1) / (NB / G), nn = (st + 1) % (NB / G) * G;
+        if (kKf == 1 ? nn == 0 : (nb == 0 && tb + 1 < kBlocks))
+          load_block(kt, kKf == 1 ? tn : tb + 1, kf[kKf == 1 ? 0 : (tb + 1) & 1]);
+        mfma_block(kf[kKf == 1 ? 0 : tn & 1], nn, acc[(st + 1) & 1]);
+      }
+      epilogue(tb, nb, acc[st & 1]);
+      if (ESZ == 2 && st + 1 < kSteps) interleave_mfma_valu<kMfmaPerStep, kValuPerMfma>();
     }
   };
 
@@ -746,12 +784,12 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     const int64_t row = tstart + lc;
     const bool okr = row >= 0 && row < a.T;
     const u32x4* src = reinterpret_cast<const u32x4*>(kb + (size_t)(okr ? row : 0) *
-                                                              Gm::kRowBytes) + lg * Gm::kSegs;
-    u32x4 kf[Gm::kSegs];
+                                                              Gm::kRowBytes) + lg * kSegs;
+    u32x4 kf[kSegs];
 #pragma unroll
-    for (int sg = 0; sg < Gm::kSegs; ++sg) kf[sg] = src[sg];
-    f32x4 acc[RB];
-    mfma_block(kf, acc);
+    for (int sg = 0; sg < kSegs; ++sg) kf[sg] = src[sg];
+    Acc acc[G];
+    mfma_block(kf, 0, acc);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       float p = 0.f;
@@ -761,20 +799,15 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       x[rb] = okr ? __float_as_uint(head_sum(p)) : 0u;
     }
   };
-  auto load_row_l2 = [&]() {
+  // lse2 of the lane's rows of block nb: padding rows hold +inf in LDS
+  auto load_row_l2 = [&](int nb, float (&l2)[kRegs]) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        int qrow;
-        row_l2[rb][i] = real_row<POS>(a, wrow0 + rb * 16 + 4 * lg + i, &qrow)
-                            ? lse_lds[wave * kRPW + rb * 16 + 4 * lg + i]
-                            : INFINITY;
-      }
+    for (int i = 0; i < kRegs; ++i) l2[i] = lse_lds[wave * kRPW + nb * M + Mm::row(i, lg)];
   };
   if (PASS2 && POS) {
     __syncthreads();   // every row's lse2 is in LDS
-    load_row_l2();
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) load_row_l2(nb, row_l2[nb]);
     if (wave_active && t_begin > 0) {
       uint32_t hx[RB];
       halo_bits(t_begin - 16, hx);
@@ -783,10 +816,11 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     }
   }
 
-  // Everything issued so far (query rows, chunk statistics, the left halo)
-  // must land before the ring's vmcnt bookkeeping starts.
+  // Everything issued so far (first tiles, query rows, chunk statistics, the
+  // left halo) must land before the ring's vmcnt bookkeeping starts.
   __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-  for (int j = 0; j < kStages - 1 && j < ntiles; ++j) issue_tile(j, j);
+  if (!kFirst)
+    for (int j = 0; j < kStages - 1 && j < ntiles; ++j) issue_tile(j, j);
 
   for (int tile = 0; tile < ntiles; ++tile) {
     const int buf = tile % kStages;
@@ -800,7 +834,10 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     // The next item is taken while the last tile is computed; no ring load
     // is in flight any more, so its latency hides behind the tile.
     if (!STATIC && tile == ntiles - 1 && tid == 0) next = take_item(a.sync);
-    if (PASS2 && !POS && tile == 0) load_row_l2();
+    if (PASS2 && !POS && kL2Regs && tile == 0) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) load_row_l2(nb, row_l2[nb]);
+    }
     // P2: the previous tile's per-wave column sums are complete; they are
     // added in wave order and the tile's importance is stored.  Numerators
     // trail by one more tile (a tile's last block is finalised in the next).
@@ -810,7 +847,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     if (!wave_active) {
       if (PASS2 && lg == 0)
 #pragma unroll
-        for (int tb = 0; tb < kBlocks; ++tb) sh.imp[tile & 1][wave][tb * 16 + lc] = 0.f;
+        for (int tb = 0; tb < kBlocks; ++tb) sh.imp[tile & 1][wave][tb * M + lc] = 0.f;
       continue;
     }
     const unsigned char* kt = &ktile[buf][0];
@@ -820,114 +857,147 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     if (PASS2) {
       // importance contribution: column sums of exp2(x - lse2) over the rows
       float* dst = &sh.imp[tile & 1][wave][lc];
-      pipelined_tile(kt, [&](int tb, const f32x4(&acc)[RB]) {
-        float part[RB];
+      if constexpr (POS) {
+        pipelined_tile(kt, [&](int tb, int, const Acc(&acc)[G]) {
+          float part[RB];
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          float p = 0.f;
+          for (int rb = 0; rb < RB; ++rb) {
+            float p = 0.f;
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            p += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[rb][i], a.c2, -row_l2[rb][i]));
-          part[rb] = p;
-        }
-        float psum = part[0];
-        if constexpr (RB >= 2) psum += part[1];
-        if constexpr (RB >= 4)
-          psum += part[2] + part[3];
-        else if constexpr (RB == 3)
-          psum += part[2];
-#pragma unroll
-        for (int rb = 4; rb < RB; ++rb) psum += part[rb];
-        const float sum = sum_lane_groups(psum);
-        if (lg == 0) dst[tb * 16] = sum;
-        if constexpr (POS) {
-          const bool okp = tok0 + tb * 16 + lc < a.T;
+            for (int i = 0; i < 4; ++i)
+              p += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[rb][i], a.c2, -row_l2[rb][i]));
+            part[rb] = p;
+          }
+          float psum = part[0];
+          if constexpr (RB >= 2) psum += part[1];
+          if constexpr (RB >= 4)
+            psum += part[2] + part[3];
+          else if constexpr (RB == 3)
+            psum += part[2];
+          const float sum = sum_lane_groups(psum);
+          if (lg == 0) dst[tb * 16] = sum;
+          // (Columns past the sequence end repeat its last row, which every
+          // window that reaches them holds already.)
           uint32_t x[RB];
 #pragma unroll
-          for (int rb = 0; rb < RB; ++rb) x[rb] = okp ? __float_as_uint(head_sum(part[rb])) : 0u;
+          for (int rb = 0; rb < RB; ++rb) x[rb] = __float_as_uint(head_sum(part[rb]));
           pool_block(x, tile, tb);
-        }
-      });
+        });
+      } else {
+        float psum = 0.f;   // of the column block's row blocks so far
+        pipelined_tile(kt, [&](int tb, int nb0, const Acc(&acc)[G]) {
+          float part[G];
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            float l2[kRegs];
+            if constexpr (!kL2Regs) load_row_l2(nb0 + g, l2);
+            // four partial sums of every fourth register
+            float p[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < kRegs; ++i) {
+              const float r = kL2Regs ? row_l2[kL2Regs ? nb0 + g : 0][i] : l2[i];
+              const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[g][i], a.c2, -r));
+              if (kRegs == 4)
+                p[0] = i == 0 ? e : p[0] + e;
+              else
+                p[i & 3] = i < 4 ? e : p[i & 3] + e;
+            }
+            part[g] = kRegs == 4 ? p[0] : (p[0] + p[1]) + (p[2] + p[3]);
+          }
+          float s = part[0];
+#pragma unroll
+          for (int g = 1; g < G; ++g) s += part[g];
+          psum = nb0 == 0 ? s : psum + s;
+          if (nb0 + G == NB) {
+            const float sum = M == 16 ? sum_lane_groups(psum) : sum_lane_halves(psum);
+            if (lg == 0) dst[tb * M] = sum;
+          }
+        });
+      }
       continue;
     }
 
-    // P1.  Each row's reference maximum m is the maximum over the first 16
-    // positions of the chunk, the same in the 16 lanes that hold the row; the
+    // P1.  Each row's reference maximum m is the maximum over the first M
+    // positions of the chunk, the same in the lanes that hold the row; the
     // fast path then adds exp2(x - m) with m fixed.  A row whose sum passes
     // 2^100 (a logit far above m) sends the whole tile to the slow path, from
     // the sums saved before it; below that, fp32 keeps full relative
     // precision, so a fixed m costs nothing.
+    const int left = (int)(t_end - tok0 < TT ? t_end - tok0 : TT) - Mm::row(0, lg);
+    auto in_chunk = [&](int tb, int i) { return tb * M + Mm::row(i, 0) < left; };
     if (tile == 0) {
-      f32x4 acc[RB];
-      column_block(kt, 0, acc);
-      const bool valid = tok0 + lc < t_end;
+      u32x4 kf[kSegs];
+      load_block(kt, 0, kf);
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
+      for (int nb = 0; nb < NB; nb += G) {
+        Acc acc[G];
+        mfma_block(kf, nb, acc);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          st_m[rb][i] = row16_max(valid ? acc[rb][i] * a.c2 : -INFINITY);
-    }
-    bool redo = false;
-    {
-      float zp[RB][4];
+        for (int g = 0; g < G; ++g) {
+          float m = -INFINITY;
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) zp[rb][i] = st_z[rb][i];
-      if (full) {
-        pipelined_tile(kt, [&](int, const f32x4(&acc)[RB]) {
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              st_z[rb][i] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[rb][i], a.c2, -st_m[rb][i]));
-        });
-      } else {
-        // Ragged tail: positions past the chunk end are masked out.
-        pipelined_tile(kt, [&](int tb, const f32x4(&acc)[RB]) {
-          const bool valid = tok0 + tb * 16 + lc < t_end;
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              st_z[rb][i] += __builtin_amdgcn_exp2f(
-                  valid ? __builtin_fmaf(acc[rb][i], a.c2, -st_m[rb][i]) : -INFINITY);
-        });
+          for (int i = 0; i < kRegs; ++i)
+            m = fmaxf(m, in_chunk(0, i) ? acc[g][i] * a.c2 : -INFINITY);
+          st_m[nb + g] = M == 16 ? max_lane_groups(m) : max_lane_halves(m);
+        }
       }
+    }
+    // (the ragged tail of a sequence takes the slow path too: it masks)
+    bool redo = !full;
+    if (full) {
+      float zp[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) zp[nb] = st_z[nb];
+      pipelined_tile(kt, [&](int, int nb0, const Acc(&acc)[G]) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          float p[4];
+#pragma unroll
+          for (int i = 0; i < kRegs; ++i) {
+            const float e = __builtin_amdgcn_exp2f(
+                __builtin_fmaf(acc[g][i], a.c2, -st_m[nb0 + g]));
+            p[i & 3] = i < 4 ? e : p[i & 3] + e;
+          }
+          st_z[nb0 + g] += (p[0] + p[1]) + (p[2] + p[3]);
+        }
+      });
       bool over = false;
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) over |= !(st_z[rb][i] <= 0x1p100f);
+      for (int nb = 0; nb < NB; ++nb) over |= !(st_z[nb] <= 0x1p100f);
       if (__any(over)) {
         redo = true;
-        per_lane_max = true;
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) st_z[rb][i] = zp[rb][i];
+        for (int nb = 0; nb < NB; ++nb) st_z[nb] = zp[nb];
       }
     }
     if (redo) {
-      // Slow path: a new large maximum.  Online max / rescale per column
-      // block and lane, padding masked; from here on the lanes of a row hold
+      // Slow path: a new large maximum.  Online max / rescale per block and
+      // lane, padding masked; from here on the lanes of a row may hold
       // different maxima.
-#pragma unroll
+#pragma unroll 1
       for (int tb = 0; tb < kBlocks; ++tb) {
-        f32x4 acc[RB];
-        column_block(kt, tb, acc);
-        const bool valid = tok0 + tb * 16 + lc < t_end;
+        u32x4 kf[kSegs];
+        load_block(kt, tb, kf);
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
+        for (int nb = 0; nb < NB; nb += G) {
+          Acc acc[G];
+          mfma_block(kf, nb, acc);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float x = valid ? acc[rb][i] * a.c2 : -INFINITY;
-            const float mn = fmaxf(st_m[rb][i], x);
+          for (int g = 0; g < G; ++g) {
+            float x[kRegs], mn = st_m[nb + g];
+#pragma unroll
+            for (int i = 0; i < kRegs; ++i) {
+              x[i] = in_chunk(tb, i) ? acc[g][i] * a.c2 : -INFINITY;
+              mn = fmaxf(mn, x[i]);
+            }
             const float ms = (mn == -INFINITY) ? 0.f : mn;
-            st_z[rb][i] = st_z[rb][i] * __builtin_amdgcn_exp2f(st_m[rb][i] - ms) +
-                          __builtin_amdgcn_exp2f(x - ms);
-            st_m[rb][i] = mn;
+            float z = st_z[nb + g] * __builtin_amdgcn_exp2f(st_m[nb + g] - ms);
+#pragma unroll
+            for (int i = 0; i < kRegs; ++i) z += __builtin_amdgcn_exp2f(x[i] - ms);
+            st_z[nb + g] = z;
+            st_m[nb + g] = mn;
           }
+        }
       }
     }
   }
@@ -958,28 +1028,20 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     return;
   }
 
-  // ---- P1: fold the 16 lane columns, publish per-chunk row statistics ------
-  // With one maximum per row the sums simply add (DPP); after a slow-path
-  // tile the (max, sum) pairs are merged with rescaling.
+  // ---- P1: merge the lane groups of each row, publish its chunk statistics --
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
+  for (int nb = 0; nb < NB; ++nb) {
+    float m = st_m[nb], z = st_z[nb];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float m = st_m[rb][i], z = st_z[rb][i];
-      if (!per_lane_max) {
-        z = row16_sum(z);
-      } else {
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) {
-          const float mo = __shfl_xor(m, off);
-          const float zo = __shfl_xor(z, off);
-          lse_merge(m, z, mo, zo);
-        }
-      }
-      const int row = wrow0 + rb * 16 + 4 * lg + i;
-      if (lc == 0 && row < a.Rp)
-        put_f2(a.partial + ((size_t)u * a.chunks + chunk) * a.Rp + row, make_float2(m, z));
+    for (int off = M; off < 64; off <<= 1) {
+      const float mo = __shfl_xor(m, off);
+      const float zo = __shfl_xor(z, off);
+      lse_merge(m, z, mo, zo);
     }
+    const int row = wrow0 + nb * M + lc;
+    if (lg == 0 && row < a.Rp)
+      put_f2(a.partial + ((size_t)u * a.chunks + chunk) * a.Rp + row, make_float2(m, z));
+  }
   if constexpr (!STATIC) {
     stores_done_barrier();
     if (tid == 0) {
@@ -1080,7 +1142,7 @@ __global__ void zero_words(uint32_t* __restrict__ p, int64_t n) {
 
 // Resident workgroups per CU of one kernel instantiation, cached per device.
 std::mutex g_occ_mu;
-int g_occ[64][2][2][4][2][8][2];
+int g_occ[64][2][2][4][2][9][2];
 int g_cus[64];
 
 // Row-group partial sums of a call into its outputs.
@@ -1127,30 +1189,52 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
     cus = g_cus[dev];
   }
   const int resident = per_cu * cus;
-  int per_unit[kMaxStages];
-  // Item size: the largest that gives the resident workgroups more P1 items
-  // than there are workgroups.  With exactly one each, every P1 item runs in
+  constexpr int TT = TileTokens<ESZ, D, W>::value;
+  const int64_t groups = (int64_t)p.units * p.row_groups;
+  // Queue item size: the largest that gives the resident workgroups more P1
+  // items than there are workgroups.  With exactly one each, every P1 item runs in
   // the first round and every P2 item in the second, with nothing to overlap
   // the second pass's re-reads of K (8 layers x 8 KV heads x 65536
   // positions: 476 us at 2048 positions against 512 us at 4096).
-  // Calls whose items of kMinChunkTokens positions would not occupy the
-  // resident workgroups twice over run as two plain launches instead: the
-  // chunk is cut so that one item per resident workgroup covers the call, and
-  // the launch boundary stands in for the queue, its clearing kernel (5 us) and
-  // the waits.  Whole calls against the queue: one layer x 8 KV heads x
-  // 8192 positions 72.6 -> 40.8 us, 24 x 8 x 4096 with 32 rows 139 -> 85 us, the
-  // fp32 2 x 512 call 65 -> 22 us.  Above the line the queue's overlap of the two
-  // passes is worth more: 36 x 8 x 8192 (2304 items for 512 workgroups) 461 us
-  // queued, 490 us as two launches.
-  constexpr int TT = TileTokens<ESZ, D, W>::value;
-  const int64_t groups = (int64_t)p.units * p.row_groups;
-  if (groups * ((p.T + kMinChunkTokens - 1) / kMinChunkTokens) <= 2 * resident) {
-    int64_t c = (groups * p.T + resident - 1) / resident;
-    const int64_t least = (p.T + p.chunks - 1) / p.chunks;   // what the workspace holds
-    if (c < least) c = least;
-    c = (c + TT - 1) / TT * TT;
-    a.chunk_tokens = (int)c;
-    a.chunks = (int)((p.T + c - 1) / c);
+  int queue_tokens = kMinChunkTokens;
+  for (int c = kMaxChunkTokens; c > kMinChunkTokens; c /= 2)
+    if (groups * ((p.T + c - 1) / c) > resident) {
+      queue_tokens = c;
+      break;
+    }
+  // Two plain launches, or the queue: whichever keeps a workgroup busy for
+  // fewer positions, an item counting kItemTokens more than it holds (an
+  // item costs 4 us beside its 28 positions per us at 256 bf16 rows).  The
+  // launches go in whole rounds of resident workgroups, of one to four as
+  // the chunks allow; the queue packs items of both passes and adds its
+  // clearing kernel, but is never shorter than one item of each.
+  // Whole calls, queue and launches: one layer x 8 KV heads x 8192 positions
+  // 72.6, 40.8 us; 24 x 8 x 4096 with 32 rows 139, 85 us; 2 x 512 in fp32 65,
+  // 22 us; 8 x 8 x 65536 with 128 rows 660, 637 us (one round of 4096); but
+  // 36 x 8 x 8192 472, 481 us (three rounds of 1664, the best of eleven
+  // cuts).
+  constexpr int64_t kItemTokens = 128;
+  const int64_t queue_items = groups * ((p.T + queue_tokens - 1) / queue_tokens);
+  int64_t queue_cost = 2 * (groups * p.T + queue_items * kItemTokens) / resident;
+  if (queue_cost < 2 * (queue_tokens + kItemTokens)) queue_cost = 2 * (queue_tokens + kItemTokens);
+  queue_cost += kItemTokens;
+  int64_t launch_tokens = 0, launch_cost = queue_cost + 1;
+  for (int rounds = 1; rounds <= 4; ++rounds) {
+    int64_t n = (int64_t)rounds * resident / groups;
+    if (n < 1) continue;
+    if (n > p.chunks) n = p.chunks;   // what the workspace holds
+    const int64_t c = ((p.T + n - 1) / n + TT - 1) / TT * TT;
+    n = (p.T + c - 1) / c;
+    const int64_t r = (groups * n + resident - 1) / resident;
+    const int64_t cost = 2 * r * (c + kItemTokens) + (n > 16 ? kItemTokens : 0);
+    if (cost < launch_cost) {
+      launch_cost = cost;
+      launch_tokens = c;
+    }
+  }
+  if (launch_cost <= queue_cost) {
+    a.chunk_tokens = (int)launch_tokens;
+    a.chunks = (int)((p.T + launch_tokens - 1) / launch_tokens);
     // Folding up to 16 chunks in every second-pass workgroup costs less than
     // a launch for it (8 chunks: 22.3 against 24.4 us for the whole call).
     if (a.chunks <= 16) a.lse2 = nullptr;
@@ -1167,12 +1251,8 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
     if (e != hipSuccess) return e;
     return finish_row_groups<POS>(p, a, s);
   }
-  a.chunk_tokens = kMinChunkTokens;
-  for (int c = kMaxChunkTokens; c > kMinChunkTokens; c /= 2)
-    if ((int64_t)p.units * p.row_groups * ((p.T + c - 1) / c) > resident) {
-      a.chunk_tokens = c;
-      break;
-    }
+  int per_unit[kMaxStages];
+  a.chunk_tokens = queue_tokens;
   a.chunks = (int)((p.T + a.chunk_tokens - 1) / a.chunk_tokens);
   per_unit[kStageP1] = a.chunks * p.row_groups;
   per_unit[kStageP2] = a.chunks * p.row_groups;
@@ -1205,6 +1285,10 @@ hipError_t launch_shape(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
   }
   if constexpr (!POS) {
     if (p.waves == 4 && p.rb == 5) return launch_w<ESZ, D, 4, POS, 5, PM>(p, a, s);
+    if constexpr (ESZ == 2) {
+      if (p.waves == 4 && p.rb == 6) return launch_w<ESZ, D, 4, POS, 6, PM>(p, a, s);
+      if (p.waves == 4 && p.rb == 8) return launch_w<ESZ, D, 4, POS, 8, PM>(p, a, s);
+    }
   }
   return hipErrorInvalidValue;
 }
