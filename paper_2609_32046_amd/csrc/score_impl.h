@@ -264,6 +264,18 @@ __device__ __forceinline__ float max_lane_groups(float v) {
   return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
 
+// The sums of a and of b over the four lane groups: a's in lane groups 0 and
+// 2, b's in 1 and 3.  Two swaps for both values, added in sum_lane_groups'
+// order.
+__device__ __forceinline__ float sum_two_lane_groups(float a, float b) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b),
+                                                  false, false);
+  const float s = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s),
+                                                  false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+
 // v plus its value in the paired lane group (lanes l and l^16), the same in
 // both lanes.
 __device__ __forceinline__ float sum_lane_pairs(float v) {
@@ -429,9 +441,6 @@ __device__ __forceinline__ bool real_row(const PersistArgs& a, int rho, int* qro
   return r < a.m && h < a.G;
 }
 
-// PM (position variant): 0 reads the power mode and head grouping from the
-// arguments; 1 fixes p = 2 and groups of four query heads at compile time,
-// so the per-block pooling epilogue has no run-time branches.
 // 32 x 32 blocks wherever a wave's bf16 rows allow, 16 x 16 for odd counts of
 // 16 rows, fp32, and the pooling pass (whose windows run across the 16 lanes
 // of a DPP row).  A 32 x 32 block takes half the MFMA issue slots and half the
@@ -441,7 +450,13 @@ struct BlockDim {
   static constexpr int value = (ESZ == 2 && RB % 2 == 0 && !POOL) ? 32 : 16;
 };
 
-template <int ESZ, int D, int W, int RB, bool PASS2, bool POS, int PM = 0, bool STATIC = false>
+// Power mode and head grouping (log2 of the padded heads) of the pooling pass.
+template <int MODE, int GSHIFT>
+struct Power {
+  static constexpr int kMode = MODE, kGshift = GSHIFT;
+};
+
+template <int ESZ, int D, int W, int RB, bool PASS2, bool POS, bool STATIC = false>
 __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
                                            Shared<ESZ, D, W, POS, RB>& sh) {
   constexpr int M = BlockDim<ESZ, RB, PASS2 && POS>::value;
@@ -449,8 +464,6 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   using Acc = typename Mm::Acc;
   constexpr int kRegs = Mm::kRegs;
   constexpr int NB = 16 * RB / M;                // M-row blocks per wave
-  const int pow_mode = PM == 1 ? (int)kPowSquare : a.pow_mode;
-  const int gshift = PM == 1 ? 2 : a.gshift;
   constexpr int kRPW = 16 * RB;                  // query rows per wave
   constexpr int kGroupRows = kRowsPerGroup;
   constexpr int TT = TileTokens<ESZ, D, W>::value;   // positions per K tile
@@ -665,7 +678,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       float s = 0.f;
       for (int w = 0; w < num_waves; ++w) {
         const float v = sh.num[POS ? tile % 3 : 0][w][POS ? t : 0];
-        s = pow_mode == kPowMax ? fmaxf(s, v) : s + v;
+        s = a.pow_mode == kPowMax ? fmaxf(s, v) : s + v;
       }
       num_out[pos] = sh.ok ? s : __builtin_nanf("");
     }
@@ -703,7 +716,8 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   constexpr int kSteps = kBlocks * (NB / G);
   constexpr int kKf = NB * M <= 64 ? 2 : 1;   // K fragment sets (registers)
   constexpr int kMfmaPerStep = G * kSegs * (ESZ == 4 ? 4 : 1);
-  constexpr int kValuPerMfma = 3 * G * kRegs / kMfmaPerStep;
+  // (the pooling epilogue has twice the importance's instructions)
+  constexpr int kValuPerMfma = (PASS2 && POS ? 6 : 3) * G * kRegs / kMfmaPerStep;
   auto pipelined_tile = [&](const unsigned char* kt, auto&& epilogue) {
     u32x4 kf[kKf][kSegs];
     Acc acc[2][G];
@@ -734,37 +748,38 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   // the chunk's two ends are computed separately from K in global memory.
   uint32_t r4p[RB] = {};   // right4 of the previous block
   uint32_t pc[RB] = {};    // previous block pooled, except the next block's part
-  auto head_sum = [&](float v) { return gshift == 3 ? sum_lane_pairs(v) : v; };
-  // Numerator terms of a finalised block, summed over this wave's tokens
-  // (or their maximum at p = inf), into the tile's LDS slot.
-  auto store_numer = [&](int btile, int btb, const uint32_t(&fin)[RB]) {
+  // Numerator terms of a finalised block, summed over this lane's tokens (or
+  // their maximum at p = inf).
+  auto numer = [&](auto power, const uint32_t(&fin)[RB]) {
+    constexpr int kMode = decltype(power)::kMode;
     float acc = 0.f;
-    if (pow_mode == kPowSquare) {
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
+    for (int rb = 0; rb < RB; ++rb) {
+      if constexpr (kMode == kPowSquare) {
         const float t = __uint_as_float(fin[rb]) * a.sq_scale;
         acc = __builtin_fmaf(t, t, acc);
-      }
-    } else if (pow_mode == kPowGeneral) {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
+      } else if constexpr (kMode == kPowGeneral) {
         acc += __builtin_amdgcn_exp2f(__builtin_fmaf(
             a.pow_p, __builtin_amdgcn_logf(__uint_as_float(fin[rb])), a.pow_kappa));
-    } else {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) acc = fmaxf(acc, __uint_as_float(fin[rb]));
+      } else {
+        acc = fmaxf(acc, __uint_as_float(fin[rb]));
+      }
     }
-    if (pow_mode == kPowMax) {
-      acc = max_lane_groups(acc);
-    } else {
-      if (gshift == 3 && (lg & 1)) acc = 0.f;   // the paired lane group holds the same tokens
-      acc = sum_lane_groups(acc);
-    }
-    if (lg == 0) sh.num[POS ? btile % 3 : 0][wave][POS ? btb * 16 + lc : 0] = acc;
+    // (with eight heads the paired lane group holds the same tokens)
+    return decltype(power)::kGshift == 3 && kMode != kPowMax && (lg & 1) ? 0.f : acc;
   };
-  // Pool a new block x: finalise the previous one, keep this one's parts.
-  auto pool_block = [&](const uint32_t(&x)[RB], int tile, int tb) {
-    uint32_t fin[RB];
+  // A wave's column sums of one block and numerators of the block before it
+  // go to LDS in one store of all lanes, lane groups 0 and 2 the sum, 1 and 3
+  // the numerator, with no branch in the tile: each lane's address for block 0
+  // (whose predecessor is the last block of the tile before; before the first
+  // tile that lands in a slot that is written again before it is read) and,
+  // 16 positions a block further, for the others.
+  auto numer_slot = [&](int tile, int tb) {
+    return &sh.num[POS ? (tile + 3) % 3 : 0][wave][POS ? tb * 16 + lc : 0];
+  };
+  // Pool a new block x: finalise the previous one into fin, keep this one's
+  // parts.
+  auto pool_block = [&](const uint32_t (&x)[RB], uint32_t (&fin)[RB]) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       const uint32_t l4 = left4(x[rb]), r4 = right4(x[rb]);
@@ -772,11 +787,49 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       pc[rb] = umax(umax(l4, r4), row_shl<13>(r4p[rb]));   // lanes 0..2 see 13..15 before
       r4p[rb] = r4;
     }
-    if (tb > 0) {
-      store_numer(tile, tb - 1, fin);
-    } else if (tile > 0) {
-      store_numer(tile - 1, kBlocks - 1, fin);
-    }
+  };
+  // Column sums and pooled numerators of a tile.
+  auto pos_tile = [&](auto power, const unsigned char* kt, int tile, auto&& pipeline) {
+    constexpr int kMode = decltype(power)::kMode;
+    float* const imp0 = &sh.imp[tile & 1][wave][lc];
+    float* const first = (lg & 1) ? numer_slot(tile - 1, kBlocks - 1) : imp0;
+    float* const rest = (lg & 1) ? numer_slot(tile, 0) : imp0 + 16;
+    pipeline(kt, [&](int tb, int, const Acc(&acc)[G]) {
+      float part[RB];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        float p;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[rb][i], a.c2, -row_l2[rb][i]));
+          p = i == 0 ? e : p + e;
+        }
+        part[rb] = p;
+      }
+      float psum = part[0];
+      if constexpr (RB >= 2) psum += part[1];
+      if constexpr (RB >= 4)
+        psum += part[2] + part[3];
+      else if constexpr (RB == 3)
+        psum += part[2];
+      // (Columns past the sequence end repeat its last row, which every
+      // window that reaches them holds already.)
+      uint32_t x[RB], fin[RB];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+        x[rb] = __float_as_uint(decltype(power)::kGshift == 3 ? sum_lane_pairs(part[rb])
+                                                              : part[rb]);
+      pool_block(x, fin);
+      const float nu = numer(power, fin);
+      float v;
+      if constexpr (kMode == kPowMax) {
+        const float all = sum_lane_groups(psum), top = max_lane_groups(nu);
+        v = (lg & 1) ? top : all;
+      } else {
+        v = sum_two_lane_groups(psum, nu);
+      }
+      (tb == 0 ? first : rest + (tb - 1) * 16)[0] = v;
+    });
   };
   // Weights of the block of 16 positions from tstart, from K in global memory
   // (positions outside [0, T) weigh 0).
@@ -796,7 +849,8 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         p += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[rb][i], a.c2, -row_l2[rb][i]));
-      x[rb] = okr ? __float_as_uint(head_sum(p)) : 0u;
+      if (a.gshift == 3) p = sum_lane_pairs(p);
+      x[rb] = okr ? __float_as_uint(p) : 0u;
     }
   };
   // lse2 of the lane's rows of block nb: padding rows hold +inf in LDS
@@ -856,34 +910,22 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
 
     if (PASS2) {
       // importance contribution: column sums of exp2(x - lse2) over the rows
-      float* dst = &sh.imp[tile & 1][wave][lc];
       if constexpr (POS) {
-        pipelined_tile(kt, [&](int tb, int, const Acc(&acc)[G]) {
-          float part[RB];
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb) {
-            float p = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              p += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[rb][i], a.c2, -row_l2[rb][i]));
-            part[rb] = p;
-          }
-          float psum = part[0];
-          if constexpr (RB >= 2) psum += part[1];
-          if constexpr (RB >= 4)
-            psum += part[2] + part[3];
-          else if constexpr (RB == 3)
-            psum += part[2];
-          const float sum = sum_lane_groups(psum);
-          if (lg == 0) dst[tb * 16] = sum;
-          // (Columns past the sequence end repeat its last row, which every
-          // window that reaches them holds already.)
-          uint32_t x[RB];
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb) x[rb] = __float_as_uint(head_sum(part[rb]));
-          pool_block(x, tile, tb);
-        });
+        // The choice between the modes stands outside the tile, whose blocks
+        // are then one straight line: a branch in each cut it into pieces
+        // and left no MFMA to run beside the pooling.
+        if (a.pow_mode == kPowMax) {
+          a.gshift == 3 ? pos_tile(Power<kPowMax, 3>{}, kt, tile, pipelined_tile)
+                        : pos_tile(Power<kPowMax, 2>{}, kt, tile, pipelined_tile);
+        } else if (a.pow_mode == kPowSquare) {
+          a.gshift == 3 ? pos_tile(Power<kPowSquare, 3>{}, kt, tile, pipelined_tile)
+                        : pos_tile(Power<kPowSquare, 2>{}, kt, tile, pipelined_tile);
+        } else {
+          a.gshift == 3 ? pos_tile(Power<kPowGeneral, 3>{}, kt, tile, pipelined_tile)
+                        : pos_tile(Power<kPowGeneral, 2>{}, kt, tile, pipelined_tile);
+        }
       } else {
+        float* dst = &sh.imp[tile & 1][wave][lc];
         float psum = 0.f;   // of the column block's row blocks so far
         pipelined_tile(kt, [&](int tb, int nb0, const Acc(&acc)[G]) {
           float part[G];
@@ -1008,7 +1050,16 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     uint32_t fin[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) fin[rb] = umax(pc[rb], row_shr<13>(left4(hx[rb])));
-    store_numer(ntiles - 1, kBlocks - 1, fin);
+    float nu;
+    if (a.pow_mode == kPowMax)
+      nu = max_lane_groups(numer(Power<kPowMax, 2>{}, fin));
+    else if (a.pow_mode == kPowSquare)
+      nu = sum_lane_groups(a.gshift == 3 ? numer(Power<kPowSquare, 3>{}, fin)
+                                         : numer(Power<kPowSquare, 2>{}, fin));
+    else
+      nu = sum_lane_groups(a.gshift == 3 ? numer(Power<kPowGeneral, 3>{}, fin)
+                                         : numer(Power<kPowGeneral, 2>{}, fin));
+    *numer_slot(ntiles - 1, kBlocks - 1) = nu;
   }
   __syncthreads();
 
@@ -1051,7 +1102,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   }
 }
 
-template <int ESZ, int D, int W, bool POS, int RB, int PM = 0>
+template <int ESZ, int D, int W, bool POS, int RB>
 // bf16: two waves per SIMD (<= 256 registers per lane) so one wave's MFMAs
 // overlap another's exp/VALU epilogue.
 __global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void persistent_kernel(PersistArgs a) {
@@ -1062,8 +1113,8 @@ __global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void persistent_kernel(Pe
   while (item < a.wl.items) {
     const Item it = decode(a.wl, item);
     switch (it.stage) {
-      case kStageP1: score_item<ESZ, D, W, RB, false, POS, PM>(a, it.unit, it.sub, sh); break;
-      case kStageP2: score_item<ESZ, D, W, RB, true, POS, PM>(a, it.unit, it.sub, sh); break;
+      case kStageP1: score_item<ESZ, D, W, RB, false, POS>(a, it.unit, it.sub, sh); break;
+      case kStageP2: score_item<ESZ, D, W, RB, true, POS>(a, it.unit, it.sub, sh); break;
       default:   // not reached: every item index below wl.items decodes
         if (threadIdx.x == 0) sh.next = take_item(a.sync);
         break;
@@ -1077,7 +1128,7 @@ __global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void persistent_kernel(Pe
 // to the same XCD (workgroups are dealt to the eight XCDs in turn), whose L2
 // then serves its query rows.  The second pass takes the items last first, so
 // that it starts on the keys the first pass read last.
-template <int ESZ, int D, int W, bool POS, int RB, int PM, bool PASS2>
+template <int ESZ, int D, int W, bool POS, int RB, bool PASS2>
 __global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void pass_kernel(PersistArgs a) {
   __shared__ Shared<ESZ, D, W, POS, RB> sh;
   if (!PASS2)   // the words later launches of the call count in
@@ -1089,7 +1140,7 @@ __global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void pass_kernel(PersistA
   if (item >= n) return;
   if (PASS2) item = n - 1 - item;
   const int u = item / per_unit;
-  score_item<ESZ, D, W, RB, PASS2, POS, PM, true>(a, u, item - u * per_unit, sh);
+  score_item<ESZ, D, W, RB, PASS2, POS, true>(a, u, item - u * per_unit, sh);
 }
 
 // lse2[row] of every query row from its chunks' (max, sum) pairs: eight
@@ -1142,7 +1193,7 @@ __global__ void zero_words(uint32_t* __restrict__ p, int64_t n) {
 
 // Resident workgroups per CU of one kernel instantiation, cached per device.
 std::mutex g_occ_mu;
-int g_occ[64][2][2][4][2][9][2];
+int g_occ[64][2][2][4][2][9];
 int g_cus[64];
 
 // Row-group partial sums of a call into its outputs.
@@ -1164,7 +1215,7 @@ hipError_t finish_row_groups(const ScorePlan& p, const PersistArgs& a, hipStream
   return e;
 }
 
-template <int ESZ, int D, int W, bool POS, int RB = 4, int PM = 0>
+template <int ESZ, int D, int W, bool POS, int RB = 4>
 hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -1174,10 +1225,10 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
   int per_cu = 0, cus = 0;
   {
     std::lock_guard<std::mutex> lock(g_occ_mu);
-    int& occ = g_occ[dev][ESZ == 2][D == 128][wi][POS][RB][PM];
+    int& occ = g_occ[dev][ESZ == 2][D == 128][wi][POS][RB];
     if (occ == 0) {
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(&persistent_kernel<ESZ, D, W, POS, RB, PM>), W * 64, 0);
+          &occ, reinterpret_cast<const void*>(&persistent_kernel<ESZ, D, W, POS, RB>), W * 64, 0);
       if (e != hipSuccess) return e;
       if (occ < 1) occ = 1;
     }
@@ -1240,13 +1291,13 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
     if (a.chunks <= 16) a.lse2 = nullptr;
     a.sync_words = (int)p.sync_words;
     const unsigned g = (unsigned)((groups * a.chunks + 7) / 8 * 8);
-    pass_kernel<ESZ, D, W, POS, RB, PM, false><<<g, W * 64, 0, s>>>(a);
+    pass_kernel<ESZ, D, W, POS, RB, false><<<g, W * 64, 0, s>>>(a);
     if (a.lse2) {
       const int64_t rows = (int64_t)p.units * p.Rp;
       fold_stats<<<(unsigned)((rows + 31) / 32), 256, 0, s>>>(a.partial, a.lse2, a.chunks, a.Rp,
                                                               rows);
     }
-    pass_kernel<ESZ, D, W, POS, RB, PM, true><<<g, W * 64, 0, s>>>(a);
+    pass_kernel<ESZ, D, W, POS, RB, true><<<g, W * 64, 0, s>>>(a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return finish_row_groups<POS>(p, a, s);
@@ -1260,46 +1311,37 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
   const int64_t grid = a.wl.items < resident ? a.wl.items : resident;
   zero_words<<<(unsigned)((p.sync_words + 255) / 256 < 1024 ? (p.sync_words + 255) / 256 : 1024),
                256, 0, s>>>(a.sync, (int64_t)p.sync_words);
-  persistent_kernel<ESZ, D, W, POS, RB, PM><<<(unsigned)grid, W * 64, 0, s>>>(a);
+  persistent_kernel<ESZ, D, W, POS, RB><<<(unsigned)grid, W * 64, 0, s>>>(a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   return finish_row_groups<POS>(p, a, s);
 }
 
-template <int ESZ, int D, bool POS, int PM>
-hipError_t launch_shape(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
+template <int ESZ, int D, bool POS>
+hipError_t launch_d(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
   switch (10 * p.waves + p.rb) {
-    case 11: return launch_w<ESZ, D, 1, POS, 1, PM>(p, a, s);
-    case 12: return launch_w<ESZ, D, 1, POS, 2, PM>(p, a, s);
-    case 14: return launch_w<ESZ, D, 1, POS, 4, PM>(p, a, s);
-    case 24: return launch_w<ESZ, D, 2, POS, 4, PM>(p, a, s);
-    case 44: return launch_w<ESZ, D, 4, POS, 4, PM>(p, a, s);
-    case 84: return launch_w<ESZ, D, 8, POS, 4, PM>(p, a, s);
+    case 11: return launch_w<ESZ, D, 1, POS, 1>(p, a, s);
+    case 12: return launch_w<ESZ, D, 1, POS, 2>(p, a, s);
+    case 14: return launch_w<ESZ, D, 1, POS, 4>(p, a, s);
+    case 24: return launch_w<ESZ, D, 2, POS, 4>(p, a, s);
+    case 44: return launch_w<ESZ, D, 4, POS, 4>(p, a, s);
+    case 84: return launch_w<ESZ, D, 8, POS, 4>(p, a, s);
   }
   if constexpr (ESZ == 2) {
     switch (10 * p.waves + p.rb) {
-      case 13: return launch_w<ESZ, D, 1, POS, 3, PM>(p, a, s);
-      case 23: return launch_w<ESZ, D, 2, POS, 3, PM>(p, a, s);
-      case 43: return launch_w<ESZ, D, 4, POS, 3, PM>(p, a, s);
+      case 13: return launch_w<ESZ, D, 1, POS, 3>(p, a, s);
+      case 23: return launch_w<ESZ, D, 2, POS, 3>(p, a, s);
+      case 43: return launch_w<ESZ, D, 4, POS, 3>(p, a, s);
     }
   }
   if constexpr (!POS) {
-    if (p.waves == 4 && p.rb == 5) return launch_w<ESZ, D, 4, POS, 5, PM>(p, a, s);
+    if (p.waves == 4 && p.rb == 5) return launch_w<ESZ, D, 4, POS, 5>(p, a, s);
     if constexpr (ESZ == 2) {
-      if (p.waves == 4 && p.rb == 6) return launch_w<ESZ, D, 4, POS, 6, PM>(p, a, s);
-      if (p.waves == 4 && p.rb == 8) return launch_w<ESZ, D, 4, POS, 8, PM>(p, a, s);
+      if (p.waves == 4 && p.rb == 6) return launch_w<ESZ, D, 4, POS, 6>(p, a, s);
+      if (p.waves == 4 && p.rb == 8) return launch_w<ESZ, D, 4, POS, 8>(p, a, s);
     }
   }
   return hipErrorInvalidValue;
-}
-
-template <int ESZ, int D, bool POS>
-hipError_t launch_d(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
-  // the paper's default score (p = 2) with four query heads per KV head
-  if constexpr (POS) {
-    if (a.pow_mode == kPowSquare && a.gshift == 2) return launch_shape<ESZ, D, true, 1>(p, a, s);
-  }
-  return launch_shape<ESZ, D, POS, 0>(p, a, s);
 }
 
 }  // namespace

@@ -57,3 +57,19 @@ def test_position_launch_shapes(torch, cb, orc, shape, p, alpha):   # noqa: F811
     q = W.gen_q(w)
     K, _ = W.gen_kv(w, want_v=False)
     check_position(orc, w, q, K, run_position(torch, cb, w, q, K, p, alpha), p, alpha, str(shape))
+
+
+@pytest.mark.parametrize("q_heads,m", [(3, 40), (7, 20), (8, 5)])   # 160, 160 and 40 rows
+@pytest.mark.parametrize("T", [15, 16, 17, 128, 129, 257, 385, 513])
+@pytest.mark.parametrize("p,alpha", [(2.0, 2.0), (3.0, 1.0), (float("inf"), 1.0)])
+def test_position_pooling_modes(torch, cb, orc, q_heads, m, T, p, alpha):   # noqa: F811
+    """Every power mode and head grouping, with one to five tiles in a chunk: a
+    block's numerators are stored while the next block is computed, across
+    tiles and chunk ends."""
+    shape = (1, q_heads, 1, 128, T, m, 1, "bf16")
+    w = W.custom(layers=1, q_heads=q_heads, kv_heads=1, head_dim=128, q_len=m, seq_len=T,
+                 senders=1, dtype="bf16", cfg_id=413)
+    say(f"case {shape} p={p}")
+    q = W.gen_q(w)
+    K, _ = W.gen_kv(w, want_v=False)
+    check_position(orc, w, q, K, run_position(torch, cb, w, q, K, p, alpha), p, alpha, str(shape))
