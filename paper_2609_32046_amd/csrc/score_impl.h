@@ -41,18 +41,19 @@
 //
 // Score items run the contraction on bf16 (fp32 for fp32 inputs) MFMA with
 // fp32 accumulation.  Each wavefront holds 16*RB query rows in registers
-// (RB = 1 to 5 row blocks, so that a unit's rows fill one, two or four waves
+// (RB = 1 to 8, so that a unit's rows fill one, two or four waves
 // with few padding rows; make_score_plan);
 // K tiles of 64 or 128 positions are staged through an LDS ring (XOR-swizzled 16-byte
 // chunks so B-fragment reads are bank-conflict free) and shared by every
 // wave of the workgroup.  The contraction index is permuted consistently for
-// Q and K: lane group j (lanes 16j..16j+15) holds a contiguous quarter of
-// each row, so every fragment is one 16-byte load.  The scale is applied in
+// Q and K: each lane group (of 16 lanes, or of 32 for 32 x 32 blocks) holds a
+// contiguous share of each row, so every fragment is one 16-byte load.  The scale is applied in
 // fp32 to the accumulator (folded with log2 e), never to bf16 operands.
 #include <math.h>
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -716,9 +717,10 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   constexpr int kSteps = kBlocks * (NB / G);
   constexpr int kKf = NB * M <= 64 ? 2 : 1;   // K fragment sets (registers)
   constexpr int kMfmaPerStep = G * kSegs * (ESZ == 4 ? 4 : 1);
-  // (the pooling epilogue has twice the importance's instructions)
-  constexpr int kValuPerMfma = (PASS2 && POS ? 6 : 3) * G * kRegs / kMfmaPerStep;
-  auto pipelined_tile = [&](const unsigned char* kt, auto&& epilogue) {
+  // `valu`: VALU instructions of the epilogue per accumulator register that the
+  // hints spread over the MFMAs.
+  auto pipelined_tile = [&](const unsigned char* kt, auto valu, auto&& epilogue) {
+    constexpr int kValuPerMfma = decltype(valu)::value * G * kRegs / kMfmaPerStep;
     u32x4 kf[kKf][kSegs];
     Acc acc[2][G];
     load_block(kt, 0, kf[0]);
@@ -794,7 +796,11 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     float* const imp0 = &sh.imp[tile & 1][wave][lc];
     float* const first = (lg & 1) ? numer_slot(tile - 1, kBlocks - 1) : imp0;
     float* const rest = (lg & 1) ? numer_slot(tile, 0) : imp0 + 16;
-    pipeline(kt, [&](int tb, int, const Acc(&acc)[G]) {
+    // The general power's epilogue is twice the importance's: six per register
+    // there (p = 3, eight heads 420 -> 400 us a call), but three with p = 2
+    // (four heads 449 us against 454).
+    constexpr int kValu = kMode == kPowGeneral ? 6 : 3;
+    pipeline(kt, std::integral_constant<int, kValu>{}, [&](int tb, int, const Acc(&acc)[G]) {
       float part[RB];
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
@@ -913,7 +919,9 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       if constexpr (POS) {
         // The choice between the modes stands outside the tile, whose blocks
         // are then one straight line: a branch in each cut it into pieces
-        // and left no MFMA to run beside the pooling.
+        // and left no MFMA to run beside the pooling, which bounds this pass by
+        // its VALU instructions (whole calls, 36 x 8 units x 8192 with p = 2: 465
+        // -> 449 us; 3 x 288 units x 3001 with p = 3 and eight heads: 466 -> 400).
         if (a.pow_mode == kPowMax) {
           a.gshift == 3 ? pos_tile(Power<kPowMax, 3>{}, kt, tile, pipelined_tile)
                         : pos_tile(Power<kPowMax, 2>{}, kt, tile, pipelined_tile);
@@ -927,7 +935,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       } else {
         float* dst = &sh.imp[tile & 1][wave][lc];
         float psum = 0.f;   // of the column block's row blocks so far
-        pipelined_tile(kt, [&](int tb, int nb0, const Acc(&acc)[G]) {
+        pipelined_tile(kt, std::integral_constant<int, 3>{}, [&](int tb, int nb0, const Acc(&acc)[G]) {
           float part[G];
 #pragma unroll
           for (int g = 0; g < G; ++g) {
@@ -990,7 +998,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       float zp[NB];
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) zp[nb] = st_z[nb];
-      pipelined_tile(kt, [&](int, int nb0, const Acc(&acc)[G]) {
+      pipelined_tile(kt, std::integral_constant<int, 3>{}, [&](int, int nb0, const Acc(&acc)[G]) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
           float p[4];
