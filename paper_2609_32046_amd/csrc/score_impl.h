@@ -796,9 +796,10 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     float* const imp0 = &sh.imp[tile & 1][wave][lc];
     float* const first = (lg & 1) ? numer_slot(tile - 1, kBlocks - 1) : imp0;
     float* const rest = (lg & 1) ? numer_slot(tile, 0) : imp0 + 16;
-    // The general power's epilogue is twice the importance's: six per register
-    // there (p = 3, eight heads 420 -> 400 us a call), but three with p = 2
-    // (four heads 449 us against 454).
+    // Six instructions a register for the general power, whose epilogue is twice
+    // the importance's, three otherwise: whole calls of 443 us with p = 2 and
+    // 418 us with p = 3 (the shapes below), 449 and 420 us with three in every
+    // mode, 441 of a start of 453 (against 443 of 467) and 400 us with six.
     constexpr int kValu = kMode == kPowGeneral ? 6 : 3;
     pipeline(kt, std::integral_constant<int, kValu>{}, [&](int tb, int, const Acc(&acc)[G]) {
       float part[RB];
@@ -921,7 +922,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
         // are then one straight line: a branch in each cut it into pieces
         // and left no MFMA to run beside the pooling, which bounds this pass by
         // its VALU instructions (whole calls, 36 x 8 units x 8192 with p = 2: 465
-        // -> 449 us; 3 x 288 units x 3001 with p = 3 and eight heads: 466 -> 400).
+        // -> 443 us; 3 x 288 units x 3001 with p = 3 and eight heads: 466 -> 418).
         if (a.pow_mode == kPowMax) {
           a.gshift == 3 ? pos_tile(Power<kPowMax, 3>{}, kt, tile, pipelined_tile)
                         : pos_tile(Power<kPowMax, 2>{}, kt, tile, pipelined_tile);
