@@ -25,6 +25,11 @@ constexpr int kMaxRows = 1024;
 // items spend less of their time filling and draining the K ring.
 constexpr int kMinChunkTokens = 1024;
 constexpr int kMaxChunkTokens = 4096;
+// Positions of one item of a plain launch at most: a row's sum over an item is
+// a chain of fp32 additions, one a K tile of at least 32 positions and so no
+// longer than the 256 of a queue item in 16-position steps.  As one item, 131072
+// equal keys after a strong first one were up to 2e-4 off (below 5e-6 so).
+constexpr int kMaxItemTokens = 8192;
 // Stages of the persistent kernel's work list, in dependency order, each
 // with chunks*row_groups items per unit:
 //   P1   per-chunk row statistics (max, sum of exp2)

@@ -8,7 +8,7 @@
 // are S = scale * Q K^T (R x T).  Importance is the column sum of the row
 // softmax, I[t] = sum_r exp(S[r,t] - lse_r).  Because every row carries its
 // own normaliser, no column sum can start before the whole row is known, so
-// K is traversed twice, chunk by chunk (1024 to 4096 positions):
+// K is traversed twice, chunk by chunk (an LDS tile to 8192 positions):
 //
 //   P1 (stats):   per row and chunk, the max and sum of exp2 in log2 units.
 //   P2 (reduce):  fold the unit's chunk statistics in fixed chunk order into
@@ -971,8 +971,8 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     // P1.  Each row's reference maximum m is the maximum over the first M
     // positions of the chunk, the same in the lanes that hold the row; the
     // fast path then adds exp2(x - m) with m fixed.  A row whose sum passes
-    // 2^100 (a logit far above m) sends the whole tile to the slow path, from
-    // the sums saved before it; below that, fp32 keeps full relative
+    // 2^100 (a logit far above m) sends the whole tile to the slow path; below
+    // that, fp32 keeps full relative
     // precision, so a fixed m costs nothing.
     const int left = (int)(t_end - tok0 < TT ? t_end - tok0 : TT) - Mm::row(0, lg);
     auto in_chunk = [&](int tb, int i) { return tb * M + Mm::row(i, 0) < left; };
@@ -996,10 +996,12 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     // (the ragged tail of a sequence takes the slow path too: it masks)
     bool redo = !full;
     if (full) {
-      float zp[NB];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) zp[nb] = st_z[nb];
-      pipelined_tile(kt, std::integral_constant<int, 3>{}, [&](int, int nb0, const Acc(&acc)[G]) {
+      // The tile's sum, then one addition to the row's: the chain of additions
+      // is as long as the item has tiles.  (Equal addends, whose rounding is the
+      // same every time, were up to 2e-5 off in items of 131072 positions added
+      // block by block.)
+      float z[NB];
+      pipelined_tile(kt, std::integral_constant<int, 3>{}, [&](int tb, int nb0, const Acc(&acc)[G]) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
           float p[4];
@@ -1009,17 +1011,20 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
                 __builtin_fmaf(acc[g][i], a.c2, -st_m[nb0 + g]));
             p[i & 3] = i < 4 ? e : p[i & 3] + e;
           }
-          st_z[nb0 + g] += (p[0] + p[1]) + (p[2] + p[3]);
+          const float sum = (p[0] + p[1]) + (p[2] + p[3]);
+          z[nb0 + g] = tb == 0 ? sum : z[nb0 + g] + sum;
         }
       });
       bool over = false;
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) over |= !(st_z[nb] <= 0x1p100f);
-      if (__any(over)) {
-        redo = true;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) st_z[nb] = zp[nb];
+      for (int nb = 0; nb < NB; ++nb) {
+        z[nb] += st_z[nb];
+        over |= !(z[nb] <= 0x1p100f);
       }
+      redo = __any(over);
+      if (!redo)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) st_z[nb] = z[nb];
     }
     if (redo) {
       // Slow path: a new large maximum.  Online max / rescale per block and
@@ -1035,17 +1040,20 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
           mfma_block(kf, nb, acc);
 #pragma unroll
           for (int g = 0; g < G; ++g) {
-            float x[kRegs], mn = st_m[nb + g];
+            float x[kRegs], p[4], mn = st_m[nb + g];
 #pragma unroll
             for (int i = 0; i < kRegs; ++i) {
               x[i] = in_chunk(tb, i) ? acc[g][i] * a.c2 : -INFINITY;
               mn = fmaxf(mn, x[i]);
             }
             const float ms = (mn == -INFINITY) ? 0.f : mn;
-            float z = st_z[nb + g] * __builtin_amdgcn_exp2f(st_m[nb + g] - ms);
 #pragma unroll
-            for (int i = 0; i < kRegs; ++i) z += __builtin_amdgcn_exp2f(x[i] - ms);
-            st_z[nb + g] = z;
+            for (int i = 0; i < kRegs; ++i) {
+              const float e = __builtin_amdgcn_exp2f(x[i] - ms);
+              p[i & 3] = i < 4 ? e : p[i & 3] + e;
+            }
+            st_z[nb + g] = st_z[nb + g] * __builtin_amdgcn_exp2f(st_m[nb + g] - ms) +
+                           ((p[0] + p[1]) + (p[2] + p[3]));
             st_m[nb + g] = mn;
           }
         }
@@ -1284,6 +1292,7 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
     if (n < 1) continue;
     if (n > p.chunks) n = p.chunks;   // what the workspace holds
     const int64_t c = ((p.T + n - 1) / n + TT - 1) / TT * TT;
+    if (c > kMaxItemTokens) continue;
     n = (p.T + c - 1) / c;
     const int64_t r = (groups * n + resident - 1) / resident;
     const int64_t cost = 2 * r * (c + kItemTokens) + (n > 16 ? kItemTokens : 0);

@@ -73,3 +73,34 @@ def test_position_pooling_modes(torch, cb, orc, q_heads, m, T, p, alpha):   # no
     q = W.gen_q(w)
     K, _ = W.gen_kv(w, want_v=False)
     check_position(orc, w, q, K, run_position(torch, cb, w, q, K, p, alpha), p, alpha, str(shape))
+
+
+def test_long_rows_of_equal_keys(torch, cb, orc):   # noqa: F811
+    """A strong first key and 131071 equal ones, with as many units as workgroups
+    are resident: each row's sum adds equal values, whose rounding is the same
+    every time, so its error grows with the length of the chain of additions.
+    Row r's first logit is v_r, all others are 0: the normaliser is
+    log(exp(v_r) + T - 1).  At most 256 additions of tile sums in an item (2^-24
+    each, 1.5e-5), as items of 4096 positions in 16-position steps had; in items
+    of the whole row the errors reach 2e-4."""
+    L, Hkv, G, D, m, S, T = 32, 8, 4, 64, 64, 2, 131072
+    lay = cb.layout(L, G * Hkv, Hkv, D, m, T, senders=S, dtype="bf16")
+    say(f"case {S * L * Hkv} x {T}")
+    v = 5.5 + np.arange(G * m) / 24.0   # 5.5 .. 16.1
+    q = torch.zeros((L, Hkv, G * m, D), device="cuda")
+    q[..., 0] = torch.from_numpy(v).to(q)
+    q = q.to(torch.bfloat16).reshape(L, G * Hkv, m, D)
+    v = q[0, :G, :, 0].reshape(-1).double()   # logit v * 8 / sqrt(64)
+    k = torch.zeros((S, L, Hkv, T, D), dtype=torch.bfloat16, device="cuda")
+    k[..., 0, 0] = 8.0
+    imp = torch.empty((S, L, Hkv, T), device="cuda")
+    lse = torch.empty((S, L, G * Hkv, m), device="cuda")
+    ws = torch.empty(cb.cb_score_workspace_bytes(lay), dtype=torch.uint8, device="cuda")
+    cb.cb_score(q, k, lay, imp, lse, ws)
+    z = torch.exp(v) + (T - 1)
+    err = (lse.reshape(-1, G * m).double() - torch.log(z)).abs().max().item()
+    rest = (1.0 / z).sum()
+    imp_err = (imp[..., 1:].double().sub_(rest).abs_().max() / rest).item()
+    say(f"  lse error {err:.2e}, importance error {imp_err:.2e}")
+    # fp32 lse of up to 24 in log2 units (2^-20), then exp2 of it
+    assert err < 1.5e-5 + 2e-6 and imp_err < 1.5e-5 + 2e-6
