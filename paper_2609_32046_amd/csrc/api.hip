@@ -468,6 +468,30 @@ int cb_gather_rows(const void* rows, int64_t senders, int64_t T, int64_t row_byt
              : CB_ERR_HIP;
 }
 
+// How a call of this layout runs its score passes, for tests (not part of the
+// C ABI): out = {device queue, positions per item, waves per workgroup, 16-row
+// blocks per wave, row groups, chunks the workspace holds}.  resident[0], [1]:
+// workgroups of the queue kernel and of the plain launches that are resident at
+// a time; NULL: the current device's.
+int cb_internal_score_form(const cb_layout* lay, int position, const int* resident,
+                           int64_t out[6]) {
+  const int st = check_layout(lay);
+  if (st != CB_OK) return st;
+  if (!out) return CB_ERR_NULL;
+  cb::ScorePlan p;
+  if (!plan_for(lay, &p, position != 0)) return CB_ERR_SHAPE;
+  cb::ScoreForm f;
+  if (resident) {
+    f = cb::choose_form(p, resident[0], resident[1]);
+  } else {
+    cb::PersistArgs a{};
+    if (cb::launch_persistent(p, a, nullptr, &f) != hipSuccess) return CB_ERR_HIP;
+  }
+  const int64_t v[6] = {f.queue, f.chunk_tokens, p.waves, p.rb, p.row_groups, p.chunks};
+  for (int i = 0; i < 6; ++i) out[i] = v[i];
+  return CB_OK;
+}
+
 const char* cb_status_string(int status) {
   switch (status) {
     case CB_OK: return "ok";

@@ -19,16 +19,15 @@ constexpr int kMaxWaves = 8;
 constexpr int kRowsPerGroup = kRowsPerWave * kMaxWaves;
 // Rows per unit (G*m) the score path accepts.
 constexpr int kMaxRows = 1024;
-// Sender positions per score work item: the largest of kMaxChunkTokens,
-// ..., kMinChunkTokens (powers of two) that still gives the resident
-// workgroups more items of the first pass than there are workgroups; larger
-// items spend less of their time filling and draining the K ring.
+// Sender positions per score item: kQueueTokens for the persistent kernel, up to
+// kMaxItemTokens for plain launches (choose_form in score.hip); the workspace
+// always has room for items of kMinChunkTokens.
 constexpr int kMinChunkTokens = 1024;
-constexpr int kMaxChunkTokens = 4096;
-// Positions of one item of a plain launch at most: a row's sum over an item is
-// a chain of fp32 additions, one a K tile of at least 32 positions and so no
-// longer than the 256 of a queue item in 16-position steps.  As one item, 131072
-// equal keys after a strong first one were up to 2e-4 off (below 5e-6 so).
+constexpr int kQueueTokens = 4096;
+// A row's sum over an item is a chain of fp32 additions, one a K tile of at
+// least 32 positions and so no longer than the 256 of 4096 positions in
+// 16-position steps.  As one item, 131072 equal keys after a strong first one
+// were up to 2e-4 off (below 5e-6 so).
 constexpr int kMaxItemTokens = 8192;
 // Stages of the persistent kernel's work list, in dependency order, each
 // with chunks*row_groups items per unit:
@@ -101,6 +100,29 @@ struct ScorePlan {
 bool make_score_plan(int L, int Hq, int Hkv, int D, int m, int S, int64_t T, int dtype,
                      float scale, bool position, ScorePlan* plan);
 
+// K positions per LDS tile of a score workgroup of `waves` waves (esz bytes an
+// element, head dimension d): 128 for bf16 workgroups of four or more waves
+// (half the per-tile barrier, wait and address work per position, two
+// 32 KiB ring stages), 8 KiB for one-wave workgroups (so that eight of them,
+// two waves per SIMD, fit the 160 KiB LDS; 16 KiB tiles left one), but no less
+// than two column blocks, else kTileTokens.
+__host__ __device__ constexpr int tile_tokens(int esz, int d, int waves) {
+  return waves == 1 ? (8192 / (d * esz) < 32 ? 32 : 8192 / (d * esz))
+         : (esz == 2 && waves >= 4) ? 2 * kTileTokens
+                                    : kTileTokens;
+}
+
+// How the score passes of one call run (choose_form): as the persistent kernel
+// with its device queue, or as one plain launch a pass, with `chunk_tokens`
+// positions an item.
+struct ScoreForm {
+  bool queue;
+  int chunk_tokens;
+};
+// queue_resident, resident: workgroups of the persistent kernel and of the
+// plain launches that the device holds at a time.
+ScoreForm choose_form(const ScorePlan& p, int queue_resident, int resident);
+
 // Power used by the numerator of the correction (position variant).
 enum PowMode : int { kPowSquare = 0, kPowGeneral = 1, kPowMax = 2 };
 
@@ -141,15 +163,17 @@ struct PersistArgs {
   WorkList wl;
 };
 
-// Zeroes the synchronisation words and launches the persistent kernel on
-// `s`; with row_groups > 1 the row-group partial sums are added into
-// importance afterwards.
-hipError_t launch_persistent(const ScorePlan& p, PersistArgs& a, hipStream_t s);
+// Launches the score passes on `s` in the form choose_form gives, the
+// synchronisation words cleared first; with row_groups > 1 the row-group
+// partial sums are added into importance afterwards.  With `only` the form is
+// stored there and nothing is launched.
+hipError_t launch_persistent(const ScorePlan& p, PersistArgs& a, hipStream_t s,
+                             ScoreForm* only = nullptr);
 // Per element size (bytes) and head dimension; instantiated in score_*.hip.
 template <int ESZ, int D>
-hipError_t launch_score_d(const ScorePlan& p, PersistArgs& a, hipStream_t s);
+hipError_t launch_score_d(const ScorePlan& p, PersistArgs& a, hipStream_t s, ScoreForm* only);
 template <int ESZ, int D>
-hipError_t launch_position_d(const ScorePlan& p, PersistArgs& a, hipStream_t s);
+hipError_t launch_position_d(const ScorePlan& p, PersistArgs& a, hipStream_t s, ScoreForm* only);
 
 // err (nullable): a device word that, when nonzero at kernel start, makes
 // every unit write -1 indices instead of a selection (the score kernel's

@@ -133,15 +133,97 @@ bool make_score_plan(int L, int Hq, int Hkv, int D, int m, int S, int64_t T, int
   return true;
 }
 
-hipError_t launch_persistent(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
+// Plain launches or the queue, and the positions per item: whichever is
+// estimated to keep a workgroup busy for fewer positions, an item counting
+// kItemTokens more than it holds (its queries, its first tiles and its statistics
+// take as long).
+//
+// Launches: items that fill one to four rounds of the resident workgroups, or
+// of 1024, 2048 or 4096 positions.  A round that is only partly filled counts as
+// a whole one, but for importance calls in bf16 workgroups of one or two waves,
+// which are bound by K's bytes, three quarters of what it lacks (the workgroups
+// that are there then share a compute unit with fewer others).  320 units x 4096
+// positions x 128 rows (1024 resident): items of 1024 (1.25 rounds) 141 us, 1408
+// (0.94) 141, 2048 156; 88 x 26679 x 20 (2304 resident): 1024 (1.03) 229 us, 2048
+// 235, 4096 255; 320 x 4096 x 256 (512 resident): 1024 (2.5) 204 us, 1408 (1.9)
+// 210, 2048 (1.25) 220, 4096 250.
+//
+// The queue packs the items of both passes and ends on part of one; a last row
+// group of few rows makes its items as much shorter.  Whole calls, queue and
+// launches in us (bf16, 128 wide): 288 x 8192 x 256 365, 361; 384 x 32768 x 320
+// 2119, 2098; 96 x 44045 x 368 876, 882; 288 x 16384 x 512 1190, 1194; 320 x 4096 x
+// 256 219, 204; 8 x 8192 x 256 73, 41; eight waves: 384 x 1000 x 512 127, 155; 144 x
+// 837 x 441 66, 65; 28 x 87519 x 575 (fp32, 64 wide) 4213, 4729;
+// position-level: 864 x 3001 x 160 410, 417; 600 x 3595 x 156 344, 350; 256 x 8192 x
+// 1024 1343, 1292.
+//
+// For the calls bound by K's bytes an estimate says little: the queue's
+// workgroups drift apart and read evenly, launches start the second pass on
+// what the first read last.  Up to three rounds launches are no slower: 64 x
+// 131072 x 16 (two rounds) 762, 759; 376 x 20655 x 36 (2.2) 801, 743; 288 x 32768 x
+// 4 (2.3) 852, 856; 88 x 26679 x 20 256, 229; 1 x 131072 x 8 50, 24; beyond, the
+// queue: 256 x 65536 x 64 (four) 1498, 1532; 256 x 65536 x 128 (four) 1594, 1630;
+// 100 x 300000 x 64 (seven) 2672, 2727; but 240 x 86801 x 44 (five) 1949, 1928.
+//
+// (32-bit divisions: the rule runs on every call, and seven candidates in 64
+// bits were 0.4 us of a 10 us call.)
+ScoreForm choose_form(const ScorePlan& p, int queue_resident, int resident) {
+  constexpr uint32_t kItemTokens = 160;
+  constexpr uint64_t kMaxItems = 1u << 24;   // plain launches count items in 32 bits
+  static_assert(kMinChunkTokens == 1 << 10, "candidates by shifts");
+  const uint32_t T = (uint32_t)p.T, res = (uint32_t)resident;
+  const uint32_t groups = (uint32_t)p.units * (uint32_t)p.row_groups;
+  const uint32_t tile = (uint32_t)tile_tokens(p.dtype == 0 ? 4 : 2, p.D, p.waves);
+  const bool whole_rounds = p.position || p.waves >= 4 || p.dtype == 0;
+  const uint64_t queue_items = (uint64_t)groups * ((T + kQueueTokens - 1) / kQueueTokens);
+  ScoreForm f{true, kQueueTokens};
+  // Costs are in positions times 2 * resident.
+  uint64_t best = UINT64_MAX;
+  if (whole_rounds) {
+    const uint64_t c = T < kQueueTokens ? (T + tile - 1) / tile * tile : kQueueTokens;
+    const uint64_t rows = (uint64_t)p.row_groups * kRowsPerGroup;
+    const uint64_t work = p.row_groups > 1 ? queue_items * (uint32_t)p.Rp / rows : queue_items;
+    const uint64_t fill = work > (uint32_t)queue_resident ? work : (uint32_t)queue_resident;
+    best = 4 * fill * (c + kItemTokens) * res / (uint32_t)queue_resident + c / 4 * res;
+  } else if (queue_items > 3u * (uint32_t)queue_resident) {
+    return f;
+  }
+  uint32_t last = 0;
+  for (uint32_t i = 0; i < 7; ++i) {
+    uint32_t n = i < 4 ? (i + 1) * res / groups
+                       : (T + (kMinChunkTokens << (i - 4)) - 1) >> (10 + i - 4);
+    if (n > (uint32_t)p.chunks) n = (uint32_t)p.chunks;   // what the workspace holds
+    if (n < 1 || n == last) continue;
+    last = n;
+    const uint32_t c = ((T + n - 1) / n + tile - 1) & ~(tile - 1);
+    if (c > (uint32_t)kMaxItemTokens) continue;
+    n = (T + c - 1) / c;
+    if ((uint64_t)groups * n > kMaxItems) continue;
+    const uint32_t items = groups * n;
+    const uint64_t full = (uint64_t)((items + res - 1) / res) * res;
+    const uint64_t used = items > res ? items : res;
+    const uint64_t cost = (whole_rounds ? 4 * full : used + 3 * full) * (c + kItemTokens) +
+                          (n > 16 ? 2 * kItemTokens * res : 0);   // the statistics' launch
+    if (cost <= best) {
+      best = cost;
+      f.queue = false;
+      f.chunk_tokens = (int)c;
+    }
+  }
+  return f;
+}
+
+hipError_t launch_persistent(const ScorePlan& p, PersistArgs& a, hipStream_t s, ScoreForm* only) {
   if (p.position) {
     if (p.dtype == 1)
-      return p.D == 128 ? launch_position_d<2, 128>(p, a, s) : launch_position_d<2, 64>(p, a, s);
-    return p.D == 128 ? launch_position_d<4, 128>(p, a, s) : launch_position_d<4, 64>(p, a, s);
+      return p.D == 128 ? launch_position_d<2, 128>(p, a, s, only)
+                        : launch_position_d<2, 64>(p, a, s, only);
+    return p.D == 128 ? launch_position_d<4, 128>(p, a, s, only)
+                      : launch_position_d<4, 64>(p, a, s, only);
   }
   if (p.dtype == 1)
-    return p.D == 128 ? launch_score_d<2, 128>(p, a, s) : launch_score_d<2, 64>(p, a, s);
-  return p.D == 128 ? launch_score_d<4, 128>(p, a, s) : launch_score_d<4, 64>(p, a, s);
+    return p.D == 128 ? launch_score_d<2, 128>(p, a, s, only) : launch_score_d<2, 64>(p, a, s, only);
+  return p.D == 128 ? launch_score_d<4, 128>(p, a, s, only) : launch_score_d<4, 64>(p, a, s, only);
 }
 
 }  // namespace cb

@@ -2,5 +2,5 @@
 #include "score_impl.h"
 
 namespace cb {
-template hipError_t launch_score_d<2, 64>(const ScorePlan&, PersistArgs&, hipStream_t);
+template hipError_t launch_score_d<2, 64>(const ScorePlan&, PersistArgs&, hipStream_t, ScoreForm*);
 }  // namespace cb

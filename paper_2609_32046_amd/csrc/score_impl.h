@@ -65,18 +65,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-
-// K positions per LDS tile: 128 for bf16 workgroups of four or more waves
-// (half the per-tile barrier, wait and address work per position, two
-// 32 KiB ring stages), 8 KiB for one-wave workgroups (so that eight of them,
-// two waves per SIMD, fit the 160 KiB LDS; 16 KiB tiles left one), but no less
-// than two column blocks, else kTileTokens.
-template <int ESZ, int D, int W>
-struct TileTokens {
-  static constexpr int value = W == 1 ? (8192 / (D * ESZ) < 32 ? 32 : 8192 / (D * ESZ))
-                               : (ESZ == 2 && W >= 4) ? 2 * kTileTokens : kTileTokens;
-};
-
 template <int ESZ, int D, int TT>
 struct Geo {
   static constexpr int kRowBytes = D * ESZ;
@@ -160,7 +148,7 @@ __device__ __forceinline__ void mfma_seg(const u32x4& a, const u32x4& b,
 // after the other LDS arrays.
 template <int ESZ, int D, int W, bool POS, int RB = 4>
 struct Stages {
-  static constexpr int kTT = TileTokens<ESZ, D, W>::value;
+  static constexpr int kTT = tile_tokens(ESZ, D, W);
   static constexpr int kTile = kTT * D * ESZ;
   static constexpr int kOther = W * ((POS ? 5 : 2) * kTT + 16 * RB) * 4;
   static constexpr int kBudget = 160 * 1024 * W / 8 - kOther;
@@ -414,7 +402,7 @@ __device__ __forceinline__ Item decode(const WorkList& wl, int64_t item) {
 // LDS of one workgroup, shared by every item type.
 template <int ESZ, int D, int W, bool POS, int RB = 4>
 struct Shared {
-  static constexpr int kTT = TileTokens<ESZ, D, W>::value;
+  static constexpr int kTT = tile_tokens(ESZ, D, W);
   using Gm = Geo<ESZ, D, kTT>;
   static constexpr int kStages = Stages<ESZ, D, W, POS, RB>::value;
   unsigned char ktile[kStages][Gm::kTileBytes] __attribute__((aligned(16)));
@@ -467,7 +455,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   constexpr int NB = 16 * RB / M;                // M-row blocks per wave
   constexpr int kRPW = 16 * RB;                  // query rows per wave
   constexpr int kGroupRows = kRowsPerGroup;
-  constexpr int TT = TileTokens<ESZ, D, W>::value;   // positions per K tile
+  constexpr int TT = tile_tokens(ESZ, D, W);   // positions per K tile
   using Gm = Geo<ESZ, D, TT>;
   constexpr int kBlocks = TT / M;                // M-position column blocks per tile
   constexpr int kSegs = Gm::kChunks / Mm::kGroups;   // 16-byte chunks per lane group
@@ -1208,9 +1196,12 @@ __global__ void zero_words(uint32_t* __restrict__ p, int64_t n) {
     p[i] = 0u;
 }
 
-// Resident workgroups per CU of one kernel instantiation, cached per device.
+// Resident workgroups per CU of one instantiation's kernels, cached per device.
+struct Occupancy {
+  int queue, passes;
+};
 std::mutex g_occ_mu;
-int g_occ[64][2][2][4][2][9];
+Occupancy g_occ[64][2][2][4][2][9];
 int g_cus[64];
 
 // Row-group partial sums of a call into its outputs.
@@ -1233,77 +1224,46 @@ hipError_t finish_row_groups(const ScorePlan& p, const PersistArgs& a, hipStream
 }
 
 template <int ESZ, int D, int W, bool POS, int RB = 4>
-hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
+hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s, ScoreForm* only) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
   const int wi = W == 1 ? 0 : W == 2 ? 1 : W == 4 ? 2 : 3;
-  int per_cu = 0, cus = 0;
+  int queue_resident = 0, resident = 0;
   {
     std::lock_guard<std::mutex> lock(g_occ_mu);
-    int& occ = g_occ[dev][ESZ == 2][D == 128][wi][POS][RB];
-    if (occ == 0) {
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(&persistent_kernel<ESZ, D, W, POS, RB>), W * 64, 0);
-      if (e != hipSuccess) return e;
-      if (occ < 1) occ = 1;
+    Occupancy& occ = g_occ[dev][ESZ == 2][D == 128][wi][POS][RB];
+    if (occ.queue == 0) {
+      const void* const f[3] = {
+          reinterpret_cast<const void*>(&persistent_kernel<ESZ, D, W, POS, RB>),
+          reinterpret_cast<const void*>(&pass_kernel<ESZ, D, W, POS, RB, false>),
+          reinterpret_cast<const void*>(&pass_kernel<ESZ, D, W, POS, RB, true>)};
+      int n[3];
+      for (int i = 0; i < 3; ++i) {
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n[i], f[i], W * 64, 0);
+        if (e != hipSuccess) return e;
+        if (n[i] < 1) n[i] = 1;
+      }
+      occ.passes = n[1] < n[2] ? n[1] : n[2];
+      occ.queue = n[0];
     }
     if (g_cus[dev] == 0) {
       e = hipDeviceGetAttribute(&g_cus[dev], hipDeviceAttributeMultiprocessorCount, dev);
       if (e != hipSuccess) return e;
     }
-    per_cu = occ;
-    cus = g_cus[dev];
+    queue_resident = occ.queue * g_cus[dev];
+    resident = occ.passes * g_cus[dev];
   }
-  const int resident = per_cu * cus;
-  constexpr int TT = TileTokens<ESZ, D, W>::value;
+  const ScoreForm form = choose_form(p, queue_resident, resident);
+  if (only) {
+    *only = form;
+    return hipSuccess;
+  }
   const int64_t groups = (int64_t)p.units * p.row_groups;
-  // Queue item size: the largest that gives the resident workgroups more P1
-  // items than there are workgroups.  With exactly one each, every P1 item runs in
-  // the first round and every P2 item in the second, with nothing to overlap
-  // the second pass's re-reads of K (8 layers x 8 KV heads x 65536
-  // positions: 476 us at 2048 positions against 512 us at 4096).
-  int queue_tokens = kMinChunkTokens;
-  for (int c = kMaxChunkTokens; c > kMinChunkTokens; c /= 2)
-    if (groups * ((p.T + c - 1) / c) > resident) {
-      queue_tokens = c;
-      break;
-    }
-  // Two plain launches, or the queue: whichever keeps a workgroup busy for
-  // fewer positions, an item counting kItemTokens more than it holds (an
-  // item costs 4 us beside its 28 positions per us at 256 bf16 rows).  The
-  // launches go in whole rounds of resident workgroups, of one to four as
-  // the chunks allow; the queue packs items of both passes and adds its
-  // clearing kernel, but is never shorter than one item of each.
-  // Whole calls, queue and launches: one layer x 8 KV heads x 8192 positions
-  // 72.6, 40.8 us; 24 x 8 x 4096 with 32 rows 139, 85 us; 2 x 512 in fp32 65,
-  // 22 us; 8 x 8 x 65536 with 128 rows 660, 637 us (one round of 4096); but
-  // 36 x 8 x 8192 472, 481 us (three rounds of 1664, the best of eleven
-  // cuts).
-  constexpr int64_t kItemTokens = 128;
-  const int64_t queue_items = groups * ((p.T + queue_tokens - 1) / queue_tokens);
-  int64_t queue_cost = 2 * (groups * p.T + queue_items * kItemTokens) / resident;
-  if (queue_cost < 2 * (queue_tokens + kItemTokens)) queue_cost = 2 * (queue_tokens + kItemTokens);
-  queue_cost += kItemTokens;
-  int64_t launch_tokens = 0, launch_cost = queue_cost + 1;
-  for (int rounds = 1; rounds <= 4; ++rounds) {
-    int64_t n = (int64_t)rounds * resident / groups;
-    if (n < 1) continue;
-    if (n > p.chunks) n = p.chunks;   // what the workspace holds
-    const int64_t c = ((p.T + n - 1) / n + TT - 1) / TT * TT;
-    if (c > kMaxItemTokens) continue;
-    n = (p.T + c - 1) / c;
-    const int64_t r = (groups * n + resident - 1) / resident;
-    const int64_t cost = 2 * r * (c + kItemTokens) + (n > 16 ? kItemTokens : 0);
-    if (cost < launch_cost) {
-      launch_cost = cost;
-      launch_tokens = c;
-    }
-  }
-  if (launch_cost <= queue_cost) {
-    a.chunk_tokens = (int)launch_tokens;
-    a.chunks = (int)((p.T + launch_tokens - 1) / launch_tokens);
+  a.chunk_tokens = form.chunk_tokens;
+  a.chunks = (int)((p.T + a.chunk_tokens - 1) / a.chunk_tokens);
+  if (!form.queue) {
     // Folding up to 16 chunks in every second-pass workgroup costs less than
     // a launch for it (8 chunks: 22.3 against 24.4 us for the whole call).
     if (a.chunks <= 16) a.lse2 = nullptr;
@@ -1321,12 +1281,10 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
     return finish_row_groups<POS>(p, a, s);
   }
   int per_unit[kMaxStages];
-  a.chunk_tokens = queue_tokens;
-  a.chunks = (int)((p.T + a.chunk_tokens - 1) / a.chunk_tokens);
   per_unit[kStageP1] = a.chunks * p.row_groups;
   per_unit[kStageP2] = a.chunks * p.row_groups;
-  make_work_list(p.units, kMaxStages, per_unit, resident, &a.wl);
-  const int64_t grid = a.wl.items < resident ? a.wl.items : resident;
+  make_work_list(p.units, kMaxStages, per_unit, queue_resident, &a.wl);
+  const int64_t grid = a.wl.items < queue_resident ? a.wl.items : queue_resident;
   zero_words<<<(unsigned)((p.sync_words + 255) / 256 < 1024 ? (p.sync_words + 255) / 256 : 1024),
                256, 0, s>>>(a.sync, (int64_t)p.sync_words);
   persistent_kernel<ESZ, D, W, POS, RB><<<(unsigned)grid, W * 64, 0, s>>>(a);
@@ -1336,27 +1294,27 @@ hipError_t launch_w(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
 }
 
 template <int ESZ, int D, bool POS>
-hipError_t launch_d(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
+hipError_t launch_d(const ScorePlan& p, PersistArgs& a, hipStream_t s, ScoreForm* only) {
   switch (10 * p.waves + p.rb) {
-    case 11: return launch_w<ESZ, D, 1, POS, 1>(p, a, s);
-    case 12: return launch_w<ESZ, D, 1, POS, 2>(p, a, s);
-    case 14: return launch_w<ESZ, D, 1, POS, 4>(p, a, s);
-    case 24: return launch_w<ESZ, D, 2, POS, 4>(p, a, s);
-    case 44: return launch_w<ESZ, D, 4, POS, 4>(p, a, s);
-    case 84: return launch_w<ESZ, D, 8, POS, 4>(p, a, s);
+    case 11: return launch_w<ESZ, D, 1, POS, 1>(p, a, s, only);
+    case 12: return launch_w<ESZ, D, 1, POS, 2>(p, a, s, only);
+    case 14: return launch_w<ESZ, D, 1, POS, 4>(p, a, s, only);
+    case 24: return launch_w<ESZ, D, 2, POS, 4>(p, a, s, only);
+    case 44: return launch_w<ESZ, D, 4, POS, 4>(p, a, s, only);
+    case 84: return launch_w<ESZ, D, 8, POS, 4>(p, a, s, only);
   }
   if constexpr (ESZ == 2) {
     switch (10 * p.waves + p.rb) {
-      case 13: return launch_w<ESZ, D, 1, POS, 3>(p, a, s);
-      case 23: return launch_w<ESZ, D, 2, POS, 3>(p, a, s);
-      case 43: return launch_w<ESZ, D, 4, POS, 3>(p, a, s);
+      case 13: return launch_w<ESZ, D, 1, POS, 3>(p, a, s, only);
+      case 23: return launch_w<ESZ, D, 2, POS, 3>(p, a, s, only);
+      case 43: return launch_w<ESZ, D, 4, POS, 3>(p, a, s, only);
     }
   }
   if constexpr (!POS) {
-    if (p.waves == 4 && p.rb == 5) return launch_w<ESZ, D, 4, POS, 5>(p, a, s);
+    if (p.waves == 4 && p.rb == 5) return launch_w<ESZ, D, 4, POS, 5>(p, a, s, only);
     if constexpr (ESZ == 2) {
-      if (p.waves == 4 && p.rb == 6) return launch_w<ESZ, D, 4, POS, 6>(p, a, s);
-      if (p.waves == 4 && p.rb == 8) return launch_w<ESZ, D, 4, POS, 8>(p, a, s);
+      if (p.waves == 4 && p.rb == 6) return launch_w<ESZ, D, 4, POS, 6>(p, a, s, only);
+      if (p.waves == 4 && p.rb == 8) return launch_w<ESZ, D, 4, POS, 8>(p, a, s, only);
     }
   }
   return hipErrorInvalidValue;
@@ -1369,12 +1327,12 @@ hipError_t launch_d(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
 // own (score_<dtype>_d<D>.hip, and score_pos_<dtype>_d<D>.hip for the
 // position variant) so that they compile in parallel.
 template <int ESZ, int D>
-hipError_t launch_score_d(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
-  return launch_d<ESZ, D, false>(p, a, s);
+hipError_t launch_score_d(const ScorePlan& p, PersistArgs& a, hipStream_t s, ScoreForm* only) {
+  return launch_d<ESZ, D, false>(p, a, s, only);
 }
 template <int ESZ, int D>
-hipError_t launch_position_d(const ScorePlan& p, PersistArgs& a, hipStream_t s) {
-  return launch_d<ESZ, D, true>(p, a, s);
+hipError_t launch_position_d(const ScorePlan& p, PersistArgs& a, hipStream_t s, ScoreForm* only) {
+  return launch_d<ESZ, D, true>(p, a, s, only);
 }
 
 }  // namespace cb

@@ -3,5 +3,5 @@
 #include "score_impl.h"
 
 namespace cb {
-template hipError_t launch_position_d<4, 64>(const ScorePlan&, PersistArgs&, hipStream_t);
+template hipError_t launch_position_d<4, 64>(const ScorePlan&, PersistArgs&, hipStream_t, ScoreForm*);
 }  // namespace cb
