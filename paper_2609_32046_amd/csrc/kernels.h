@@ -103,13 +103,19 @@ bool make_score_plan(int L, int Hq, int Hkv, int D, int m, int S, int64_t T, int
 // K positions per LDS tile of a score workgroup of `waves` waves (esz bytes an
 // element, head dimension d): 128 for bf16 workgroups of four or more waves
 // (half the per-tile barrier, wait and address work per position, two
-// 32 KiB ring stages), 8 KiB for one-wave workgroups (so that eight of them,
-// two waves per SIMD, fit the 160 KiB LDS; 16 KiB tiles left one), but no less
-// than two column blocks, else kTileTokens.
-__host__ __device__ constexpr int tile_tokens(int esz, int d, int waves) {
-  return waves == 1 ? (8192 / (d * esz) < 32 ? 32 : 8192 / (d * esz))
-         : (esz == 2 && waves >= 4) ? 2 * kTileTokens
-                                    : kTileTokens;
+// 32 KiB ring stages), else kTileTokens; but one-wave workgroups of plain
+// launches and of fp32 take 8 KiB, though no less than two column blocks, so that
+// eight of them, two waves per SIMD, fit the 160 KiB LDS.  In the queue, whose
+// calls are long and bound by K's bytes, one-wave bf16 workgroups hold twice the
+// bytes in flight, four workgroups a compute unit: 256 units x 65536 positions x
+// 64 rows (128 wide) 1542 us with two stages of 8 KiB, 1500 with two of 16 KiB;
+// 240 x 86801 x 44 2009, 1948; 64 wide, four stages of 8 KiB: 736 x 37039 x 14 1368,
+// 1304 us.  Plain launches of 10 x 26829 x 16 28.5 us with
+// 8 KiB, 30.1 with 16.
+__host__ __device__ constexpr int tile_tokens(int esz, int d, int waves, bool queue) {
+  return waves == 1 && !(queue && esz == 2) ? (8192 / (d * esz) < 32 ? 32 : 8192 / (d * esz))
+         : (esz == 2 && waves >= 4)         ? 2 * kTileTokens
+                                            : kTileTokens;
 }
 
 // How the score passes of one call run (choose_form): as the persistent kernel

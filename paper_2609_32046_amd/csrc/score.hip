@@ -173,7 +173,7 @@ ScoreForm choose_form(const ScorePlan& p, int queue_resident, int resident) {
   static_assert(kMinChunkTokens == 1 << 10, "candidates by shifts");
   const uint32_t T = (uint32_t)p.T, res = (uint32_t)resident;
   const uint32_t groups = (uint32_t)p.units * (uint32_t)p.row_groups;
-  const uint32_t tile = (uint32_t)tile_tokens(p.dtype == 0 ? 4 : 2, p.D, p.waves);
+  const uint32_t tile = (uint32_t)tile_tokens(p.dtype == 0 ? 4 : 2, p.D, p.waves, false);
   const bool whole_rounds = p.position || p.waves >= 4 || p.dtype == 0;
   const uint64_t queue_items = (uint64_t)groups * ((T + kQueueTokens - 1) / kQueueTokens);
   ScoreForm f{true, kQueueTokens};

@@ -143,15 +143,23 @@ __device__ __forceinline__ void mfma_seg(const u32x4& a, const u32x4& b,
   }
 }
 
+// Waves a SIMD should hold: two, so that one wave's MFMAs overlap another's
+// exp/VALU epilogue; one for fp32 and for the queue's one-wave bf16 workgroups
+// (four a compute unit; see tile_tokens).
+constexpr int waves_per_simd(int esz, int waves, bool queue) {
+  return esz == 2 && !(waves == 1 && queue) ? 2 : 1;
+}
+
 // LDS ring depth: as many K tiles as fit the workgroup's share of the
-// 160 KiB LDS at two waves per SIMD (8/W workgroups per CU), between 2 and 4,
-// after the other LDS arrays.
-template <int ESZ, int D, int W, bool POS, int RB = 4>
+// 160 KiB LDS at two waves per SIMD (8/W workgroups per CU; at one for the
+// queue's one-wave bf16 workgroups), between 2 and 4, after the other LDS arrays.
+template <int ESZ, int D, int W, bool POS, int RB, bool QUEUE>
 struct Stages {
-  static constexpr int kTT = tile_tokens(ESZ, D, W);
+  static constexpr int kTT = tile_tokens(ESZ, D, W, QUEUE);
   static constexpr int kTile = kTT * D * ESZ;
   static constexpr int kOther = W * ((POS ? 5 : 2) * kTT + 16 * RB) * 4;
-  static constexpr int kBudget = 160 * 1024 * W / 8 - kOther;
+  static constexpr int kShare = waves_per_simd(ESZ, W, QUEUE) == 1 && ESZ == 2 ? 4 : 8;
+  static constexpr int kBudget = 160 * 1024 * W / kShare - kOther;
   static constexpr int kFit = kBudget / kTile;
   static constexpr int value = kFit < 2 ? 2 : (kFit > 4 ? 4 : kFit);
 };
@@ -400,11 +408,11 @@ __device__ __forceinline__ Item decode(const WorkList& wl, int64_t item) {
 }
 
 // LDS of one workgroup, shared by every item type.
-template <int ESZ, int D, int W, bool POS, int RB = 4>
+template <int ESZ, int D, int W, bool POS, int RB, bool QUEUE>
 struct Shared {
-  static constexpr int kTT = tile_tokens(ESZ, D, W);
+  static constexpr int kTT = tile_tokens(ESZ, D, W, QUEUE);
   using Gm = Geo<ESZ, D, kTT>;
-  static constexpr int kStages = Stages<ESZ, D, W, POS, RB>::value;
+  static constexpr int kStages = Stages<ESZ, D, W, POS, RB, QUEUE>::value;
   unsigned char ktile[kStages][Gm::kTileBytes] __attribute__((aligned(16)));
   float imp[2][W][kTT];          // P2 per-wave column sums of a tile (by tile parity)
   // Position variant: per-wave correction numerators of a tile, by tile
@@ -445,9 +453,9 @@ struct Power {
   static constexpr int kMode = MODE, kGshift = GSHIFT;
 };
 
-template <int ESZ, int D, int W, int RB, bool PASS2, bool POS, bool STATIC = false>
+template <int ESZ, int D, int W, int RB, bool PASS2, bool POS, bool QUEUE>
 __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
-                                           Shared<ESZ, D, W, POS, RB>& sh) {
+                                           Shared<ESZ, D, W, POS, RB, QUEUE>& sh) {
   constexpr int M = BlockDim<ESZ, RB, PASS2 && POS>::value;
   using Mm = Mma<M>;
   using Acc = typename Mm::Acc;
@@ -455,12 +463,12 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   constexpr int NB = 16 * RB / M;                // M-row blocks per wave
   constexpr int kRPW = 16 * RB;                  // query rows per wave
   constexpr int kGroupRows = kRowsPerGroup;
-  constexpr int TT = tile_tokens(ESZ, D, W);   // positions per K tile
+  constexpr int TT = tile_tokens(ESZ, D, W, QUEUE);   // positions per K tile
   using Gm = Geo<ESZ, D, TT>;
   constexpr int kBlocks = TT / M;                // M-position column blocks per tile
   constexpr int kSegs = Gm::kChunks / Mm::kGroups;   // 16-byte chunks per lane group
   constexpr int kPer = Gm::kTileChunks / (W * 64);   // 16-byte loads per thread per tile
-  constexpr int kStages = Stages<ESZ, D, W, POS, RB>::value;  // K tiles resident/in flight in LDS
+  constexpr int kStages = Stages<ESZ, D, W, POS, RB, QUEUE>::value;  // K tiles resident/in flight in LDS
   static_assert(Gm::kTileChunks % (W * 64) == 0, "tile must split evenly");
   auto& ktile = sh.ktile;
   float* lse_lds = sh.lse;
@@ -568,7 +576,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   // of the unit derives bitwise-identical lse2.
   if (PASS2) {
     bool ok;
-    if constexpr (STATIC) {
+    if constexpr (!QUEUE) {
       // The statistics were written by an earlier launch: nothing to wait
       // for, and only a wait limit of 0 gives up.
       ok = a.spin_limit != 0u;
@@ -590,7 +598,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
         lse_lds[lr] = INFINITY;
         continue;
       }
-      if (STATIC && a.lse2) {
+      if (!QUEUE && a.lse2) {
         const float l2 = ok ? a.lse2[(size_t)u * a.Rp + row] : __builtin_nanf("");
         lse_lds[lr] = l2;
         if (chunk == 0 && a.row_lse)
@@ -882,7 +890,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     if (tile + kStages - 1 < ntiles) issue_tile(tile + kStages - 1, (tile + kStages - 1) % kStages);
     // The next item is taken while the last tile is computed; no ring load
     // is in flight any more, so its latency hides behind the tile.
-    if (!STATIC && tile == ntiles - 1 && tid == 0) next = take_item(a.sync);
+    if (QUEUE && tile == ntiles - 1 && tid == 0) next = take_item(a.sync);
     if (PASS2 && !POS && kL2Regs && tile == 0) {
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) load_row_l2(nb, row_l2[nb]);
@@ -1074,7 +1082,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       if (ntiles > 1) flush_num(ntiles - 2);
       flush_num(ntiles - 1);
     }
-    if constexpr (!STATIC) {
+    if constexpr (QUEUE) {
       stores_done_barrier();
       if (tid == 0) {
         count_in(done2 + u);
@@ -1098,7 +1106,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     if (lg == 0 && row < a.Rp)
       put_f2(a.partial + ((size_t)u * a.chunks + chunk) * a.Rp + row, make_float2(m, z));
   }
-  if constexpr (!STATIC) {
+  if constexpr (QUEUE) {
     stores_done_barrier();
     if (tid == 0) {
       count_in(done1 + (size_t)u * a.row_groups + rg);
@@ -1108,18 +1116,17 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
 }
 
 template <int ESZ, int D, int W, bool POS, int RB>
-// bf16: two waves per SIMD (<= 256 registers per lane) so one wave's MFMAs
-// overlap another's exp/VALU epilogue.
-__global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void persistent_kernel(PersistArgs a) {
-  __shared__ Shared<ESZ, D, W, POS, RB> sh;
+__global__ __launch_bounds__(W * 64, waves_per_simd(ESZ, W, true)) void persistent_kernel(
+    PersistArgs a) {
+  __shared__ Shared<ESZ, D, W, POS, RB, true> sh;
   if (threadIdx.x == 0) sh.next = take_item(a.sync);
   __syncthreads();
   int64_t item = sh.next;
   while (item < a.wl.items) {
     const Item it = decode(a.wl, item);
     switch (it.stage) {
-      case kStageP1: score_item<ESZ, D, W, RB, false, POS>(a, it.unit, it.sub, sh); break;
-      case kStageP2: score_item<ESZ, D, W, RB, true, POS>(a, it.unit, it.sub, sh); break;
+      case kStageP1: score_item<ESZ, D, W, RB, false, POS, true>(a, it.unit, it.sub, sh); break;
+      case kStageP2: score_item<ESZ, D, W, RB, true, POS, true>(a, it.unit, it.sub, sh); break;
       default:   // not reached: every item index below wl.items decodes
         if (threadIdx.x == 0) sh.next = take_item(a.sync);
         break;
@@ -1134,8 +1141,9 @@ __global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void persistent_kernel(Pe
 // then serves its query rows.  The second pass takes the items last first, so
 // that it starts on the keys the first pass read last.
 template <int ESZ, int D, int W, bool POS, int RB, bool PASS2>
-__global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void pass_kernel(PersistArgs a) {
-  __shared__ Shared<ESZ, D, W, POS, RB> sh;
+__global__ __launch_bounds__(W * 64, waves_per_simd(ESZ, W, false)) void pass_kernel(
+    PersistArgs a) {
+  __shared__ Shared<ESZ, D, W, POS, RB, false> sh;
   if (!PASS2)   // the words later launches of the call count in
     for (int i = blockIdx.x * (W * 64) + threadIdx.x; i < a.sync_words; i += gridDim.x * (W * 64))
       a.sync[i] = 0u;
@@ -1145,7 +1153,7 @@ __global__ __launch_bounds__(W * 64, ESZ == 2 ? 2 : 1) void pass_kernel(PersistA
   if (item >= n) return;
   if (PASS2) item = n - 1 - item;
   const int u = item / per_unit;
-  score_item<ESZ, D, W, RB, PASS2, POS, true>(a, u, item - u * per_unit, sh);
+  score_item<ESZ, D, W, RB, PASS2, POS, false>(a, u, item - u * per_unit, sh);
 }
 
 // lse2[row] of every query row from its chunks' (max, sum) pairs: eight
