@@ -19,7 +19,7 @@ constexpr int kMaxWaves = 8;
 constexpr int kRowsPerGroup = kRowsPerWave * kMaxWaves;
 // Rows per unit (G*m) the score path accepts.
 constexpr int kMaxRows = 1024;
-// Sender positions per score item: kQueueTokens for the persistent kernel, up to
+// Sender positions per score item: up to kQueueTokens for the persistent kernel, up to
 // kMaxItemTokens for plain launches (choose_form in score.hip); the workspace
 // always has room for items of kMinChunkTokens.
 constexpr int kMinChunkTokens = 1024;

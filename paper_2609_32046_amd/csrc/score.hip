@@ -82,8 +82,17 @@ bool make_score_plan(int L, int Hq, int Hkv, int D, int m, int S, int64_t T, int
   static constexpr int kShapes[][2] = {{1, 1}, {1, 2}, {1, 3}, {1, 4}, {2, 3}, {2, 4}, {4, 3},
                                        {4, 4}, {4, 5}, {4, 6}, {4, 8}, {8, 4}};
   p->row_groups = (p->Rp + kRowsPerGroup - 1) / kRowsPerGroup;
+  // 128 rows a wave only where there are more items of kMinChunkTokens than
+  // 512: an item's queries take twice as long to load into half the waves.
+  // Eight waves against four, whole calls of 512 rows: 16 x 1000 22, 26 us; 384
+  // x 1000 127, 141; 192 x 2000 122, 138; 64 x 4096 84, 87; 256 x 2048 133,
+  // 138; but 288 x 3001 (864 items) 281, 269; 800 x 512 165, 150; 32 x 65536 574,
+  // 554; 288 x 16384 1312, 1190.
+  const bool few = (int64_t)p->units * p->row_groups *
+                       ((T + kMinChunkTokens - 1) / kMinChunkTokens) <= 512;
   for (const auto& sh : kShapes) {
     if ((dtype == 0 && (sh[1] == 3 || sh[1] > 5)) || (position && sh[1] > 4)) continue;
+    if (sh[1] == 8 && few) continue;
     p->waves = sh[0];
     p->rb = sh[1];
     if (16 * sh[0] * sh[1] >= p->Rp) break;
@@ -140,30 +149,30 @@ bool make_score_plan(int L, int Hq, int Hkv, int D, int m, int S, int64_t T, int
 //
 // Launches: items that fill one to four rounds of the resident workgroups, or
 // of 1024, 2048 or 4096 positions.  A round that is only partly filled counts as
-// a whole one, but for importance calls in bf16 workgroups of one or two waves,
-// which are bound by K's bytes, three quarters of what it lacks (the workgroups
-// that are there then share a compute unit with fewer others).  320 units x 4096
-// positions x 128 rows (1024 resident): items of 1024 (1.25 rounds) 141 us, 1408
-// (0.94) 141, 2048 156; 88 x 26679 x 20 (2304 resident): 1024 (1.03) 229 us, 2048
-// 235, 4096 255; 320 x 4096 x 256 (512 resident): 1024 (2.5) 204 us, 1408 (1.9)
-// 210, 2048 (1.25) 220, 4096 250.
+// a whole one, but in bf16 workgroups of one or two waves, which are bound by
+// K's bytes, three quarters of what it lacks (the workgroups that are there then
+// share a compute unit with fewer others).  320 units x 4096 positions x 128 rows
+// (1024 resident): items of 1024 (1.25 rounds) 141 us, 1408 (0.94) 141, 2048 156;
+// 88 x 26679 x 20 (2304 resident): 1024 (1.03) 229 us, 2048 235, 4096 255; 320 x
+// 4096 x 256 (512 resident): 1024 (2.5) 204 us, 1408 (1.9) 210, 2048 (1.25) 220,
+// 4096 250.
 //
-// The queue packs the items of both passes and ends on part of one; a last row
-// group of few rows makes its items as much shorter.  Whole calls, queue and
-// launches in us (bf16, 128 wide): 288 x 8192 x 256 365, 361; 384 x 32768 x 320
-// 2119, 2098; 96 x 44045 x 368 876, 882; 288 x 16384 x 512 1190, 1194; 320 x 4096 x
-// 256 219, 204; 8 x 8192 x 256 73, 41; eight waves: 384 x 1000 x 512 127, 155; 144 x
-// 837 x 441 66, 65; 28 x 87519 x 575 (fp32, 64 wide) 4213, 4729;
-// position-level: 864 x 3001 x 160 410, 417; 600 x 3595 x 156 344, 350; 256 x 8192 x
-// 1024 1343, 1292.
+// The queue packs the items of both passes and ends on part of one.  Whole calls,
+// queue and launches in us (bf16, 128 wide): 288 x 8192 x 256 365, 361; 384 x
+// 32768 x 320 2119, 2098; 96 x 44045 x 368 876, 882; 288 x 16384 x 512 1190, 1194;
+// 320 x 4096 x 256 219, 204; 8 x 8192 x 256 73, 41; eight waves: 384 x 1000 x 512
+// 127, 155; 144 x 837 x 441 66, 65; 28 x 87519 x 575 (fp32, 64 wide) 4213, 4729;
+// position-level: 864 x 3001 x 160 410, 417; 600 x 3595 x 156 344, 350; 512 x 8192
+// x 512 1343, 1292.
 //
 // For the calls bound by K's bytes an estimate says little: the queue's
 // workgroups drift apart and read evenly, launches start the second pass on
 // what the first read last.  Up to three rounds launches are no slower: 64 x
 // 131072 x 16 (two rounds) 762, 759; 376 x 20655 x 36 (2.2) 801, 743; 288 x 32768 x
 // 4 (2.3) 852, 856; 88 x 26679 x 20 256, 229; 1 x 131072 x 8 50, 24; beyond, the
-// queue: 256 x 65536 x 64 (four) 1498, 1532; 256 x 65536 x 128 (four) 1594, 1630;
-// 100 x 300000 x 64 (seven) 2672, 2727; but 240 x 86801 x 44 (five) 1949, 1928.
+// queue: 256 x 65536 x 64 (four) 1498, 1532; 256 x 65536 x 128 (four) 1594, 1630
+// (position-level 1814, 2021); 100 x 300000 x 64 (seven) 2672, 2727; but 240 x
+// 86801 x 44 (five) 1949, 1928.
 //
 // (32-bit divisions: the rule runs on every call, and seven candidates in 64
 // bits were 0.4 us of a 10 us call.)
@@ -174,17 +183,31 @@ ScoreForm choose_form(const ScorePlan& p, int queue_resident, int resident) {
   const uint32_t T = (uint32_t)p.T, res = (uint32_t)resident;
   const uint32_t groups = (uint32_t)p.units * (uint32_t)p.row_groups;
   const uint32_t tile = (uint32_t)tile_tokens(p.dtype == 0 ? 4 : 2, p.D, p.waves, false);
-  const bool whole_rounds = p.position || p.waves >= 4 || p.dtype == 0;
+  const bool whole_rounds = p.waves >= 4 || p.dtype == 0;
   const uint64_t queue_items = (uint64_t)groups * ((T + kQueueTokens - 1) / kQueueTokens);
   ScoreForm f{true, kQueueTokens};
   // Costs are in positions times 2 * resident.
   uint64_t best = UINT64_MAX;
   if (whole_rounds) {
-    const uint64_t c = T < kQueueTokens ? (T + tile - 1) / tile * tile : kQueueTokens;
-    const uint64_t rows = (uint64_t)p.row_groups * kRowsPerGroup;
-    const uint64_t work = p.row_groups > 1 ? queue_items * (uint32_t)p.Rp / rows : queue_items;
-    const uint64_t fill = work > (uint32_t)queue_resident ? work : (uint32_t)queue_resident;
-    best = 4 * fill * (c + kItemTokens) * res / (uint32_t)queue_resident + c / 4 * res;
+    // A last row group of up to four waves has a SIMD to each: half an item.
+    const uint32_t last_rows = (uint32_t)p.Rp - (uint32_t)(p.row_groups - 1) * kRowsPerGroup;
+    const bool half = p.row_groups > 1 && last_rows <= 4 * kRowsPerWave;
+    // Smaller items only where a workgroup has its compute unit to itself, so
+    // that nothing else fills what a long one leaves idle (192 x 2000 x 512: 122
+    // us with items of 1024, 146 as one round of launches).
+    for (uint32_t q = kQueueTokens; q >= kMinChunkTokens; q /= 2) {
+      const uint64_t c = T < q ? (T + tile - 1) / tile * tile : q;
+      const uint64_t items = (uint64_t)groups * ((T + q - 1) / q);
+      const uint64_t work = half ? items * 3 / 4 : items;
+      const uint64_t fill = work > (uint32_t)queue_resident ? work : (uint32_t)queue_resident;
+      const uint64_t cost =
+          4 * fill * (c + kItemTokens) * res / (uint32_t)queue_resident + c / 4 * res;
+      if (cost < best) {
+        best = cost;
+        f.chunk_tokens = (int)q;
+      }
+      if (p.waves < kMaxWaves) break;
+    }
   } else if (queue_items > 3u * (uint32_t)queue_resident) {
     return f;
   }

@@ -64,3 +64,11 @@ def test_every_form_fits_its_workspace(form):
 def test_known_forms(form, L, Hkv, G, m, T, resident, queue):
     lay = form.layout(L, G * Hkv, Hkv, 128, m, T)
     assert bool(form(lay, False, *resident)["queue"]) == queue
+
+
+# 512 rows in eight waves of 64 up to 512 items of 1024 positions, then in four of 128
+@pytest.mark.parametrize("units,T,waves", [(512, 1000, 8), (513, 1000, 4), (256, 2048, 8),
+                                           (256, 2049, 4), (1, 2**19, 8), (1, 2**19 + 1, 4)])
+def test_waves_of_512_rows(form, units, T, waves):
+    f = form(form.layout(units, 4, 1, 128, 128, T))
+    assert (f["waves"], f["blocks"]) == (waves, 32 // waves)
