@@ -303,6 +303,8 @@ def test_sequential_chain(torch, cb, orc, relative):
 
 
 def test_position_wait_timeout_is_reported(torch, cb, orc):
+    """Plain launches at this size, whose second gives up at a wait limit of 0; the
+    device queue's waits in test_gpu_queue.py."""
     w = W.custom(layers=2, q_heads=8, kv_heads=2, head_dim=128, q_len=16, seq_len=3000, cfg_id=298)
     say("case position wait timeout")
     q = W.gen_q(w)

@@ -334,7 +334,8 @@ def test_late_large_logit_takes_the_slow_path(torch, cb, orc, dtype):
     than 100 (log2 units) pushes a row sum past the 2^100 guard, so its tile
     is redone on the online-max path and the row maxima differ between lanes:
     the rescaling merge must then give the same importance as the plain
-    definition.  Two such positions, in different chunks; every other
+    definition.  Two such positions, in different chunks (of 64 positions at this
+    size; longer ones in test_gpu_queue.py); every other
     position keeps weights far below FLT_MIN."""
     w = W.custom(layers=1, q_heads=4, kv_heads=2, head_dim=128, q_len=16, seq_len=3000,
                  dtype=dtype)
@@ -346,8 +347,8 @@ def test_late_large_logit_takes_the_slow_path(torch, cb, orc, dtype):
     base = rng.standard_normal(128).astype(np.float32)
     qf = base + 0.3 * rng.standard_normal(f32(q).shape).astype(np.float32)
     Kf = f32(K).copy()
-    Kf[..., 700, :] = 8.0 * base      # chunk 0, well past its first 16 positions
-    Kf[..., 1500, :] = 7.5 * base     # a later chunk
+    Kf[..., 700, :] = 8.0 * base      # 60 positions into its chunk
+    Kf[..., 1500, :] = 7.5 * base     # 28 into a later one
     q, K = back(qf), back(Kf)
     out = run_gpu(torch, cb, w, q, K, V, 0.25)
     assert np.all(np.isfinite(out["imp"]))
@@ -527,8 +528,9 @@ def test_split_select_timeout_is_reported(torch, cb, orc):
 
 
 def test_wait_timeout_is_reported(torch, cb, orc):
-    """With the wait limit at 0 from the host, every dependency wait of the
-    score kernel gives up at once: every kernel still exits, cb_score_status
+    """With the wait limit at 0 from the host, the second of the plain launches
+    that a call of this size runs as gives up, as every wait of the device queue
+    does (test_gpu_queue.py): every kernel still exits, cb_score_status
     reports CB_ERR_TIMEOUT, importance is NaN, cb_pipeline's selection is -1
     throughout and the compacted rows are zero.  Restoring the limit gives a
     normal run on the same workspace."""

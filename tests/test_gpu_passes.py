@@ -22,8 +22,8 @@ SHAPES = [
     (1, 1, 1, 128, 128, 97, 1, "bf16"), (1, 3, 1, 128, 1025, 43, 1, "bf16"),
     (1, 6, 1, 64, 640, 32, 1, "bf16"), (1, 1, 1, 128, 130, 193, 1, "bf16"),
     (1, 1, 1, 64, 129, 257, 1, "bf16"), (1, 3, 1, 128, 200, 107, 1, "bf16"),
-    # more than 16 chunks a unit (the statistics folded by a launch of their
-    # own): 64 and 512 chunks, and two row groups
+    # more than 16 items a unit (the statistics folded by a launch of their
+    # own): 65, 313 and 24 of them, the last with two row groups
     (1, 2, 1, 128, 4097, 8, 1, "bf16"), (1, 4, 1, 64, 40000, 4, 1, "bf16"),
     (1, 8, 1, 128, 3000, 65, 1, "bf16"),
     # fp32 in one, two and four blocks a wave
