@@ -225,9 +225,11 @@ hipError_t launch_select(const float* importance, int64_t units, int64_t T, int6
     select_vec_kernel<1024, 8><<<g, 1024, 0, s>>>(importance, T, keep, idx, err);
   } else if (T <= kBinsMaxT) {
     // Longer rows do not fit the registers of half a compute unit.  288 units:
-    // 65536 scores 86 us in registers (one workgroup a compute unit, two
-    // rounds), 61 us here; 100003 scores 504 us with every pass over L2, 86 us
-    // here.  Below the line registers win: 864 x 16384 38 against 50 us.
+    // 65536 scores 83 us in registers (one workgroup a compute unit, two
+    // rounds), 52 us here; 64 units 39, 33 us, one 38, 31; 100003 scores 502 us
+    // with every pass over L2, 78 us here.  At the line both are alike (288 x
+    // 32768 33, 33 us; 864 65, 62), below it registers win where units are many:
+    // 864 x 16384 35, 41 us.
     const size_t lds = (size_t)select_bins_words(T) * 4;
     select_bins_kernel<<<g, 1024, lds, s>>>(importance, T, keep, idx, err);
   } else if (units < compute_units()) {

@@ -695,14 +695,16 @@ __device__ __forceinline__ void select_unit_vec(const float* __restrict__ row, i
 // Rows too long to hold in registers, up to kBinsMaxT scores, in one
 // workgroup of NT threads and two reads of the row as a rule:
 //
-//   1. A sample (one score per thread) gives a key range; the first read
-//      counts every key in kBins equal bins of that range (one more bin on each
-//      side), and the bin holding the keep-th largest key becomes the new
-//      range.  Keys are the scores' bit patterns, so the bins are as fine as
-//      the scores are close: of 100003 log-normal scores the bin holds about 50.
-//      While it holds more than kBinsCap keys and spans more than one, the row
-//      is read again with the bins cut from that range (heavy ties, a
-//      threshold outside the sample).
+//   1. A sample of kSample scores gives two keys, the order statistics some
+//      ranks above and below the keep-th largest's.  The first read counts the
+//      keys above the pair and those equal to either (a wave at a time, no
+//      LDS), and every key between them in kBins equal bins.  The bin holding
+//      the keep-th largest key, or the one of the pair, becomes the new range:
+//      of 100003 log-normal scores the bin holds about three.  Ties heavy enough
+//      to meet in one bin are keys of the pair, so that any distribution reads
+//      alike.  While the range holds more than kBinsCap keys and spans more than
+//      one, the row is read again with the bins cut from it (a threshold
+//      outside the pair: the extreme ranks, a sample that is not like the row).
 //   2. The last read marks in an LDS bit mask every key above the range, and
 //      lists the keys inside it, or marks them too when the range is one key.
 //   3. The listed keys are ranked against one another by (key descending,
@@ -710,12 +712,16 @@ __device__ __forceinline__ void select_unit_vec(const float* __restrict__ row, i
 //      the mask is written out: each wave turns 64 positions into slots.
 //
 // Bound by instruction issue (about a dozen a key and read): 288 x 100003 scores
-// take 86 us, 1.3 TB/s of the row read once, where the radix passes over L2
-// took 504 us; one row alone 45 us.
+// take 78 us (85 with bins over the sample's whole range, 502 with the radix
+// passes over L2), one row alone 45 us (44, 272).  Bins over the whole range
+// also met heavy ties in one LDS word and read such rows again: 288 x 65536 with
+// seven in ten scores equal 113 us, nine in ten zero 180, all near one but for
+// one in a hundred 186; in this form 52 to 57, 83 to 113 in registers.
 // Loads are dwords, coalesced (any alignment), the next kLoads of a thread in
 // flight while the last ones are worked on.
-constexpr int kBins = 8192;          // the first and last lie outside the range
+constexpr int kBins = 8192;
 constexpr int kBinsCap = 512;
+constexpr int kSample = 256;
 constexpr int64_t kBinsMaxT = 524288;
 // LDS words: the histogram, later the two masks of ceil(T/64) 64-bit words.
 __host__ __device__ constexpr int64_t select_bins_words(int64_t T) {
@@ -731,25 +737,27 @@ __device__ __forceinline__ void select_unit_bins(const float* __restrict__ row, 
   constexpr int kOwn = kBins / NT;
   static_assert(kOwn % 4 == 0 && kOwn <= 32, "bins per thread");
   __shared__ uint32_t scratch[kWaves + 1];
-  __shared__ uint32_t red[2][kWaves];
-  __shared__ uint32_t s_bin, s_need, s_count, s_list;
-  __shared__ uint32_t c_key[kBinsCap], c_pos[kBinsCap];
+  __shared__ uint32_t s_bin, s_need, s_count, s_list, s_side[3], s_pair[2];
+  // the sample and its ranks, later the listed keys and their positions
+  __shared__ __align__(16) uint32_t c_key[kBinsCap], c_pos[kBinsCap];
+  static_assert(kSample <= kBinsCap, "sample");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
   // Every key of the row, in position order (batch, load, wave, lane).  The
-  // body gets (key, valid, load j of the batch); after(b0) ends a batch.
-  auto each = [&](auto&& body, auto&& after) {
-    float next[kLoads], raw[kLoads];
-    auto load = [&](int b0) {
+  // body gets (key, valid, load j of the batch); after(b0) ends a batch.  The
+  // first batch is requested before, by the read that came before.
+  float next[kLoads];
+  auto load = [&](int b0) {
 #pragma unroll
-      for (int j = 0; j < kLoads; ++j) {
-        const int p = b0 + j * NT + tid;
-        next[j] = row[p < T ? p : T - 1];
-      }
-    };
-    load(0);
+    for (int j = 0; j < kLoads; ++j) {
+      const int p = b0 + j * NT + tid;
+      next[j] = row[p < T ? p : T - 1];
+    }
+  };
+  auto each = [&](bool again, auto&& body, auto&& after) {
     int b0 = 0;
     for (; b0 + kLoads * NT <= T; b0 += kLoads * NT) {
+      float raw[kLoads];
 #pragma unroll
       for (int j = 0; j < kLoads; ++j) raw[j] = next[j];
       if (b0 + kLoads * NT < T) load(b0 + kLoads * NT);
@@ -762,68 +770,13 @@ __device__ __forceinline__ void select_unit_bins(const float* __restrict__ row, 
       for (int j = 0; j < kLoads; ++j) body(order_key(next[j]), b0 + j * NT + tid < T, b0, j);
       after(b0);
     }
+    if (again) load(0);
   };
 
-  // 1. the sample's range, and whether the sample repeats its ends (ties)
-  uint32_t lo, hi;
-  bool tied;
-  {
-    const uint32_t k = order_key(row[(int)((int64_t)tid * T / NT)]);
-    lo = hi = k;
-    for (int off = 32; off > 0; off >>= 1) {
-      const uint32_t a = __shfl_xor(lo, off), b = __shfl_xor(hi, off);
-      lo = a < lo ? a : lo;
-      hi = b > hi ? b : hi;
-    }
-    if (lane == 0) {
-      red[0][wave] = lo;
-      red[1][wave] = hi;
-    }
-    __syncthreads();
-    for (int w = 0; w < kWaves; ++w) {
-      lo = red[0][w] < lo ? red[0][w] : lo;
-      hi = red[1][w] > hi ? red[1][w] : hi;
-    }
-    tied = __syncthreads_count(k == lo || k == hi) > NT / 16;
-  }
-  uint32_t need = (uint32_t)keep, count;
-  for (bool first = true;; first = false) {
-    for (int i = tid; i < kBins; i += NT) hist[i] = 0u;
-    if (tid == 0) s_list = 0u;
-    __syncthreads();
-    // Bin d holds the keys base + (d << sh) and up, bin 0 also those below
-    // base and the last bin all above it.
-    int sh = 0;
-    while (((hi - lo) >> sh) > (uint32_t)kBins - 3u) ++sh;
-    const uint32_t base = !first ? lo : lo < (1u << sh) ? 0u : lo - (1u << sh);
-    const uint32_t span = hi - lo;
-    auto digit = [&](uint32_t key) {
-      const uint32_t d = ((key > base ? key : base) - base) >> sh;
-      return d < (uint32_t)kBins - 1u ? d : (uint32_t)kBins - 1u;
-    };
-    if (first && !tied) {
-      each([&](uint32_t key, bool valid, int, int) {
-        if (valid) atomicAdd(&hist[digit(key)], 1u);
-      }, [](int) {});
-    } else {
-      // Later reads count the range's keys only (what lies outside is
-      // settled); a wave of equal digits adds once.
-      each([&](uint32_t key, bool valid, int, int) {
-        const bool in = valid && (first || key - lo <= span);
-        const uint64_t m = __ballot(in);
-        if (m == 0) return;
-        const uint32_t d = digit(key);
-        const uint32_t d0 = __builtin_amdgcn_readlane(d, __ffsll((unsigned long long)m) - 1);
-        if (__ballot(in && d == d0) == m) {
-          if (lane == 0) atomicAdd(&hist[d0], (uint32_t)__popcll(m));
-        } else if (in) {
-          atomicAdd(&hist[d], 1u);
-        }
-      }, [](int) {});
-    }
-    __syncthreads();
-    // The bin with (keys above it) < need <= (keys above it or in it): thread
-    // t owns the t-th highest kOwn bins.  Reads start at a bank of their own.
+  // The bin with (keys above it) < need <= (keys above it or in it), from the
+  // highest: thread t owns the t-th highest kOwn bins, its reads start at a bank
+  // of their own.  Leaves s_bin, s_need (within the bin) and s_count.
+  auto find_bin = [&](uint32_t need) {
     const uint4* mine = reinterpret_cast<const uint4*>(hist + (NT - 1 - tid) * kOwn);
     uint32_t own = 0;
 #pragma unroll
@@ -846,19 +799,147 @@ __device__ __forceinline__ void select_unit_bins(const float* __restrict__ row, 
       }
     }
     __syncthreads();
-    const uint32_t bin = s_bin;
+  };
+  // Bins of 2^shift keys from lo on that hold all of [lo, hi]
+  auto shift_of = [](uint32_t lo, uint32_t hi) {
+    const uint32_t over = (hi - lo) / (uint32_t)kBins;
+    return over == 0 ? 0 : 32 - __clz((int)over);
+  };
+
+  // 1. The sample's order statistics four deviations to either side of the
+  //    rank that keep has in it: kParts threads a sample key count those before
+  //    it (ties by place).
+  uint32_t lo, hi;
+  bool tied;   // the sample repeats a key of the pair
+  {
+    constexpr int kParts = NT / kSample;
+    static_assert(kSample % kParts == 0 && kSample % 64 == 0, "sample parts");
+    uint32_t* sample = c_key;          // kSample keys
+    uint32_t* ranks = c_pos;
+    const int i = tid % kSample, part = tid / kSample;
+    const uint32_t k = order_key(row[(int)((int64_t)i * T / kSample)]);
+    load(0);
+    if (part == 0) {
+      sample[i] = k;
+      ranks[i] = 0u;
+    }
+    for (int j = tid; j < kBins; j += NT) hist[j] = 0u;
+    if (tid < 3) s_side[tid] = 0u;
+    if (tid == 0) s_list = 0u;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int j0 = 0; j0 < kSample / kParts; j0 += 4) {
+      const int j = part * (kSample / kParts) + j0;
+      const uint4 v = *reinterpret_cast<const uint4*>(sample + j);   // the same in every lane
+      before += (v.x > k || (v.x == k && j < i)) + (v.y > k || (v.y == k && j + 1 < i)) +
+                (v.z > k || (v.z == k && j + 2 < i)) + (v.w > k || (v.w == k && j + 3 < i));
+    }
+    atomicAdd(&ranks[i], before);
+    __syncthreads();
+    if (part == 0) {
+      const float want = (float)keep * ((float)kSample / (float)T);
+      const float off = 1.f + 4.f * sqrtf(want * fmaxf(0.f, 1.f - want / (float)kSample));
+      const int up = (int)(want - off), down = (int)(want + off) + 1;
+      const int rank = (int)ranks[i];
+      if (rank == (up < 0 ? 0 : up)) s_pair[1] = k;
+      if (rank == (down > kSample - 1 ? kSample - 1 : down)) s_pair[0] = k;
+    }
+    __syncthreads();
+    lo = s_pair[0];
+    hi = s_pair[1];
+    tied = __syncthreads_count(part == 0 && (k == lo || k == hi)) > 2 || lo == hi;
+  }
+  uint32_t need = (uint32_t)keep, count;
+  {
+    // Without ties the pair's keys go to the bins like those between them.
+    const uint32_t base = tied ? lo + 1u : lo;
+    const uint32_t inner = !tied ? hi - lo + 1u : hi - lo < 2u ? 0u : hi - base;
+    const int sh = inner != 0u ? shift_of(base, base + (inner - 1u)) : 0;
+    uint32_t n_above = 0, n_hi = 0, n_lo = 0;
+    if (tied) {
+      each(true, [&](uint32_t key, bool valid, int, int) {
+        n_above += (uint32_t)__popcll(__ballot(valid && key > hi));
+        n_hi += (uint32_t)__popcll(__ballot(valid && key == hi));
+        n_lo += (uint32_t)__popcll(__ballot(valid && key == lo));
+        const uint32_t d = key - base;
+        if (valid && d < inner) atomicAdd(&hist[d >> sh], 1u);
+      }, [](int) {});
+    } else {
+      each(true, [&](uint32_t key, bool valid, int, int) {
+        n_above += (uint32_t)__popcll(__ballot(valid && key > hi));
+        const uint32_t d = key - base;
+        if (valid && d < inner) atomicAdd(&hist[d >> sh], 1u);
+      }, [](int) {});
+    }
+    if (lane < 3) atomicAdd(&s_side[lane], lane == 0 ? n_above : lane == 1 ? n_hi : n_lo);
+    __syncthreads();
+    const uint32_t above = s_side[0], at_hi = s_side[1], at_lo = lo == hi ? 0u : s_side[2];
+    if (need <= above) {
+      lo = hi + 1u;
+      hi = 0xffffffffu;
+      count = above;
+    } else if (need <= above + at_hi) {
+      need -= above;
+      lo = hi;
+      count = at_hi;
+    } else {
+      need -= above + at_hi;
+      if (tid == 0) s_bin = (uint32_t)kBins;   // none, unless find_bin finds it
+      __syncthreads();
+      find_bin(need);
+      const uint32_t bin = s_bin;
+      if (bin < (uint32_t)kBins) {
+        need = s_need;
+        count = s_count;
+        lo = base + (bin << sh);
+        const uint32_t top = base + (inner - 1u);
+        hi = top - lo < (1u << sh) ? top : lo + ((1u << sh) - 1u);
+      } else {
+        uint32_t in_bins = 0;
+        for (int j = tid; j < kBins; j += NT) in_bins += hist[j];
+        uint32_t total;
+        block_exclusive_scan<NT>(in_bins, scratch, &total);
+        need -= total;
+        if (need <= at_lo) {
+          hi = lo;
+          count = at_lo;
+        } else {
+          need -= at_lo;
+          count = (uint32_t)T - above - at_hi - total - at_lo;
+          hi = lo - 1u;
+          lo = 0u;
+        }
+      }
+    }
+  }
+  while (count > (uint32_t)kBinsCap && lo != hi) {
+    __syncthreads();   // s_bin.. and the bins are read before this pass writes them
+    for (int i = tid; i < kBins; i += NT) hist[i] = 0u;
+    __syncthreads();
+    const int sh = shift_of(lo, hi);
+    const uint32_t span = hi - lo;
+    // The range's keys only (what lies outside is settled); a wave of equal
+    // digits adds once.
+    each(true, [&](uint32_t key, bool valid, int, int) {
+      const bool in = valid && key - lo <= span;
+      const uint64_t m = __ballot(in);
+      if (m == 0) return;
+      const uint32_t d = (key - lo) >> sh;
+      const uint32_t d0 = __builtin_amdgcn_readlane(d, __ffsll((unsigned long long)m) - 1);
+      if (__ballot(in && d == d0) == m) {
+        if (lane == 0) atomicAdd(&hist[d0], (uint32_t)__popcll(m));
+      } else if (in) {
+        atomicAdd(&hist[d], 1u);
+      }
+    }, [](int) {});
+    __syncthreads();
+    find_bin(need);
     need = s_need;
     count = s_count;
-    // The bin's keys; the outer bins of a first read reach the ends.
-    const uint64_t b_lo = (uint64_t)base + ((uint64_t)bin << sh);
-    uint64_t b_hi = b_lo + ((1ull << sh) - 1ull);
-    const uint64_t cap = first ? 0xffffffffull : (uint64_t)hi;
-    if (bin == (uint32_t)kBins - 1u || b_hi > cap) b_hi = cap;
-    lo = bin == 0u && first ? 0u : (uint32_t)b_lo;
-    hi = (uint32_t)b_hi;
-    if (count <= (uint32_t)kBinsCap || lo == hi) break;
-    __syncthreads();   // s_bin.. are read before the next pass writes them
+    lo += s_bin << sh;
+    hi = hi - lo < (1u << sh) ? hi : lo + ((1u << sh) - 1u);
   }
+  __syncthreads();   // the bins are read before the masks take their place
 
   // 2. the masks (the histogram's words), one 64-bit word per 64 positions:
   //    lane j gathers load j's words of a batch and stores them together
@@ -869,7 +950,7 @@ __device__ __forceinline__ void select_unit_bins(const float* __restrict__ row, 
   {
     const uint32_t span = hi - lo;
     uint64_t g = 0, e = 0;
-    each([&](uint32_t key, bool valid, int b0, int j) {
+    each(false, [&](uint32_t key, bool valid, int b0, int j) {
       const uint64_t gj = __ballot(valid && key > hi);
       const bool in = valid && key - lo <= span;
       if (lane == j) g = gj;
