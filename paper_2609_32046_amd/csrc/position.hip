@@ -134,6 +134,7 @@ __global__ __launch_bounds__(kTermWaves * kTermLanes) void position_terms(TermAr
   if (!(c >= 1.0)) c = 1.0;
   // Q_t = Pool_7 of the layer sums (this wave's own LDS writes), S_t = Q_t C^alpha
   qpre[lane] = q * a.q_scale;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the other lanes' values are read
   __builtin_amdgcn_wave_barrier();
   if (!in || lane < kPool || lane >= kTermLanes - kPool) return;
   double qv = qpre[lane + (int)(lo - t)];
