@@ -134,8 +134,7 @@ enum PowMode : int { kPowSquare = 0, kPowGeneral = 1, kPowMax = 2 };
 
 // Device-side synchronisation words of one call (zeroed before the launch):
 //   [0..1] work-queue head (64-bit), [2] error flag (kSyncError), [3] unused,
-//   then done1[U*row_groups] (P1 items finished per unit and row group),
-//   done2[U] (P2 items finished per unit).
+//   then done1[U*row_groups] (P1 items finished per unit and row group).
 constexpr int kSyncHeader = 4;
 constexpr int kSyncError = 2;
 

@@ -131,7 +131,7 @@ bool make_score_plan(int L, int Hq, int Hkv, int D, int m, int S, int64_t T, int
   p->sel = SelectSplit{1, 0, 0, 0};
   if (!position) select_split_plan(p->units, T, &p->sel);
   p->off_sync = off;
-  p->off_sel_counters = kSyncHeader + (size_t)p->units * p->row_groups + (size_t)p->units;
+  p->off_sel_counters = kSyncHeader + (size_t)p->units * p->row_groups;
   p->sync_words = p->off_sel_counters +
                   (p->sel.parts > 1 ? (size_t)p->units * kSplitCounterWords : 0);
   off = al(off + p->sync_words * sizeof(uint32_t));

@@ -330,12 +330,6 @@ __device__ __forceinline__ uint32_t poll_u32(const uint32_t* p) {
 __device__ __forceinline__ void count_in(uint32_t* p) {
   __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void put_f32(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float get_f32(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ void put_f2(float2* p, float2 v) {
   __hip_atomic_store(reinterpret_cast<unsigned long long*>(p),
                      __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
@@ -346,10 +340,6 @@ __device__ __forceinline__ float2 get_f2(const float2* p) {
       float2, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p),
                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
-__device__ __forceinline__ int32_t get_i32(const int32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Every wave waits for its own stores to complete, then the workgroup
 // meets; after this one thread may publish the workgroup's results.
 __device__ __forceinline__ void stores_done_barrier() {
@@ -478,7 +468,6 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   const int layer = (u / a.Hkv) % a.L;
   const int kvh = u % a.Hkv;
   uint32_t* done1 = a.sync + kSyncHeader;
-  uint32_t* done2 = done1 + (size_t)a.units * a.row_groups;
 
   // The thread index passes through an empty asm so that the per-lane
   // addresses derived from it are recomputed for each item instead of being
@@ -642,8 +631,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
   }
 
   // P2 output of one tile: the sum over waves (in wave order) of the
-  // per-wave column sums, as device-scope stores (the unit's SEL item reads
-  // them); NaN if the statistics never arrived.
+  // per-wave column sums; NaN if the statistics never arrived.
   float* imp_out = (a.row_groups > 1)
                        ? a.imp_partial + ((size_t)rg * a.units + u) * (size_t)a.T
                        : a.importance + (size_t)u * (size_t)a.T;
@@ -1082,13 +1070,7 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
       if (ntiles > 1) flush_num(ntiles - 2);
       flush_num(ntiles - 1);
     }
-    if constexpr (QUEUE) {
-      stores_done_barrier();
-      if (tid == 0) {
-        count_in(done2 + u);
-        sh.next = next;
-      }
-    }
+    if (QUEUE && tid == 0) sh.next = next;
     return;
   }
 
