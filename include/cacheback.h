@@ -22,9 +22,9 @@
  *   - cb_score and cb_pipeline enqueue, on `stream`, either a small kernel
  *     that clears the call's synchronisation words in `ws` and one persistent
  *     kernel whose resident workgroups take every work item of the call from
- *     a device queue, or, where that is shorter (small calls, or calls whose
- *     items fill whole rounds of workgroups), one kernel per score pass (and
- *     one that folds the row statistics between them).  One more kernel adds
+ *     a device queue, or one kernel per score pass (and, in short calls of
+ *     many items a unit, one that folds the row statistics between them),
+ *     whichever is estimated to be shorter.  One more kernel adds
  *     row-group sums when G*m > 512.  The persistent kernel's workgroups wait
  *     on one another through `ws`, with bounded waits; two calls sharing a
  *     workspace must not overlap.
@@ -236,9 +236,9 @@ size_t cb_position_workspace_bytes(const cb_layout* lay);
  * importance (nullable): [S][L][Hkv][T], receives cb_score's importance
  * (held in `ws` when NULL).  Computed in fp32 from bf16/fp32 inputs with
  * fp32 accumulation; sums over layers and heads in fp64.  Deterministic.
- * Enqueues the kernels of cb_score (second pass
- * extended with the pooled per-token sums), then one small kernel; calls too
- * small to fill the device run each pass as a launch of its own instead. */
+ * Enqueues the kernels of cb_score in either of its forms (second pass
+ * extended with the pooled per-token sums; two kernels add row-group sums
+ * when the padded rows exceed 512), then one small kernel. */
 int cb_position_score(const void* q, const void* k, const cb_layout* lay, double p, double alpha,
                       float* score, float* qscore, float* corr, float* importance, void* ws,
                       size_t ws_bytes, void* stream);

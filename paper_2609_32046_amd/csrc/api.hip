@@ -1,7 +1,8 @@
 // C ABI of the receiver-conditioned KV selection path: argument validation,
 // workspace carve-up and launches.  Declared in include/cacheback.h.
 //
-// cb_score enqueues one small kernel that clears the call's synchronisation
+// cb_score enqueues the two score passes as plain launches, or one small kernel
+// that clears the call's synchronisation
 // words and one persistent kernel that runs both score passes of every unit
 // from a device work queue (score.hip); more than 512 query rows per unit add
 // a row-group sum.  cb_pipeline follows it with the select and gather

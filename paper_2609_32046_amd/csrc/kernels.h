@@ -11,10 +11,9 @@ namespace cb {
 constexpr int64_t kMaxSeqLen = ((int64_t)1 << 31) - ((int64_t)1 << 16);
 // Tokens per K tile staged through LDS by the score kernels.
 constexpr int kTileTokens = 64;
-// Query rows one wavefront holds by default (four 16-row MFMA blocks).
+// Query rows one wavefront of a full row group holds (four 16-row MFMA blocks).
 constexpr int kRowsPerWave = 64;
-// Waves per score workgroup at most; rows beyond 8 waves' worth form more
-// row groups.
+// Waves per score workgroup at most; rows beyond 512 form more row groups.
 constexpr int kMaxWaves = 8;
 constexpr int kRowsPerGroup = kRowsPerWave * kMaxWaves;
 // Rows per unit (G*m) the score path accepts.
@@ -87,11 +86,11 @@ struct ScorePlan {
   int Gp;           // padded group (position variant), else G
   int Rp;           // rows the kernel iterates per unit: R, or Gp*m
   int chunks;       // chunks per unit the workspace holds
-  int rb;           // 16-row MFMA blocks per wave: 4, or 5 (see make_score_plan)
+  int rb;           // 16-row MFMA blocks per wave, 1 to 8 (see make_score_plan)
   SelectSplit sel;  // split selection of the same units (cb_pipeline)
   size_t off_sel_counters;   // in words from the sync words' start
   size_t off_sel_data;       // in bytes
-  int row_groups;   // ceil(Rp / (16 * rb * kMaxWaves))
+  int row_groups;   // ceil(Rp / kRowsPerGroup)
   int waves;        // waves per workgroup
   float c2;         // scale * log2(e)
   size_t off_partial, off_lse2, off_imp_partial, off_numer_partial, off_sync, sync_words, total_bytes;

@@ -1,6 +1,6 @@
 #pragma once
-// Receiver-conditioned importance of sender positions as one persistent
-// kernel (gfx950 / CDNA4): device code and launch templates, included by
+// Receiver-conditioned importance of sender positions in two passes over K
+// (gfx950 / CDNA4): device code and launch templates, included by
 // the per-dtype translation units score_*.hip.
 //
 // For one unit (sender s, layer l, KV head g) the query rows are the m tokens
@@ -15,17 +15,17 @@
 //                 lse2 (log2 of the row normaliser), recompute the logits and
 //                 add exp2(x - lse2) over the rows.
 //
-// Calls too small to fill the device for long run P1 and P2 as two plain
-// launches of one item per workgroup (pass_kernel; the rule is in launch_w).
-// The rest run as one persistent kernel:
+// A call runs P1 and P2 either as two plain launches of one item per workgroup
+// (pass_kernel), or as one persistent kernel with a queue, whichever choose_form
+// (score.hip) estimates to be shorter.  The latter:
 //
 // Scheduling.  Every P1 and P2 item of every unit sits in one ordered list
 // (WorkList in kernels.h); resident workgroups take items from a device
 // queue (one atomic counter) until the list is exhausted.  A P2 item waits
 // until all P1 items of its unit (and row group) are counted in, on a
 // per-unit counter.  The list places P2 of unit u lag steps after its P1, so
-// by the time a P2 item is taken its statistics are normally complete and
-// the unit's K is still in the 256 MB Infinity Cache; the whole stage is one
+// by the time a P2 item is taken its statistics are normally complete;
+// the whole stage is one
 // launch with no idle boundaries between unit groups.  Dependencies always
 // precede their dependants in the list and are taken only by running
 // workgroups, so the waits always end whatever the number of resident
@@ -43,7 +43,7 @@
 // fp32 accumulation.  Each wavefront holds 16*RB query rows in registers
 // (RB = 1 to 8, so that a unit's rows fill one, two or four waves
 // with few padding rows; make_score_plan);
-// K tiles of 64 or 128 positions are staged through an LDS ring (XOR-swizzled 16-byte
+// K tiles of 32 to 128 positions (tile_tokens) are staged through an LDS ring (XOR-swizzled 16-byte
 // chunks so B-fragment reads are bank-conflict free) and shared by every
 // wave of the workgroup.  The contraction index is permuted consistently for
 // Q and K: each lane group (of 16 lanes, or of 32 for 32 x 32 blocks) holds a
@@ -781,9 +781,9 @@ __device__ __forceinline__ void score_item(const PersistArgs& a, int u, int sub,
     float* const first = (lg & 1) ? numer_slot(tile - 1, kBlocks - 1) : imp0;
     float* const rest = (lg & 1) ? numer_slot(tile, 0) : imp0 + 16;
     // Six instructions a register for the general power, whose epilogue is twice
-    // the importance's, three otherwise: whole calls of 443 us with p = 2 and
-    // 418 us with p = 3 (the shapes below), 449 and 420 us with three in every
-    // mode, 441 of a start of 453 (against 443 of 467) and 400 us with six.
+    // the importance's, three otherwise.  Whole calls of the shapes below: p = 2
+    // takes 0.962 of its time with branches at three and 0.974 at six; p = 3 420
+    // us at three and 400 at six.
     constexpr int kValu = kMode == kPowGeneral ? 6 : 3;
     pipeline(kt, std::integral_constant<int, kValu>{}, [&](int tb, int, const Acc(&acc)[G]) {
       float part[RB];
@@ -1120,8 +1120,10 @@ __global__ __launch_bounds__(W * 64, waves_per_simd(ESZ, W, true)) void persiste
 
 // One score pass of every item, one item per workgroup: blocks of one unit go
 // to the same XCD (workgroups are dealt to the eight XCDs in turn), whose L2
-// then serves its query rows.  The second pass takes the items last first, so
-// that it starts on the keys the first pass read last.
+// then serves its query rows.  The second pass takes the items last first:
+// where they fill several rounds of workgroups it then starts on the keys the
+// first pass read last (in one round all items run at once, and the order does
+// nothing).
 template <int ESZ, int D, int W, bool POS, int RB, bool PASS2>
 __global__ __launch_bounds__(W * 64, waves_per_simd(ESZ, W, false)) void pass_kernel(
     PersistArgs a) {

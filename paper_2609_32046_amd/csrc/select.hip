@@ -6,8 +6,8 @@
 // workgroup size measured fastest for each length on MI355X: 512 threads
 // with KV = 1 or 2 up to 4096 scores, 1024 with KV = 2 up to 8192, 512 with
 // KV = 8 up to 16384 (four workgroups fit a compute unit), 1024 with KV = 8
-// up to 32768.  Rows of up to 524288 scores are read twice, with fine bins of
-// a sampled range in LDS (select_unit_bins).  Longer rows re-read the
+// up to 32768.  Rows of up to 524288 scores are read twice, with fine bins
+// between two sampled keys in LDS (select_unit_bins).  Longer rows re-read the
 // scores from L2 on every digit pass; when there are fewer units than
 // compute units they run in 1024-thread workgroups (the extra threads per
 // unit are otherwise idle hardware) whose ordered passes read the row
