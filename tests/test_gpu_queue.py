@@ -221,6 +221,8 @@ def test_queue_position_wait_timeout_is_reported(torch, cb):   # noqa: F811
     (8, 4, 32, 128, 65536, "bf16", 0), (8, 4, 40, 128, 65536, "bf16", 0),
     (8, 4, 64, 64, 65536, "bf16", 0), (8, 4, 128, 128, 131072, "bf16", 0),
     (8, 4, 16, 128, 65536, "f32", 0),
+    # 36 items a unit, folded by every second-pass workgroup (no launch of their own)
+    (64, 4, 4, 64, 70000, "bf16", 0),
     (1600, 4, 4, 64, 4200, "bf16", 1), (1600, 4, 8, 64, 4200, "bf16", 1),
     (560, 4, 40, 128, 700, "bf16", 1), (560, 4, 64, 128, 700, "bf16", 1),
     (600, 4, 128, 128, 700, "bf16", 1), (1080, 4, 8, 128, 700, "f32", 1)])
