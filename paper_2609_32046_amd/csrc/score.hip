@@ -157,7 +157,9 @@ bool make_score_plan(int L, int Hq, int Hkv, int D, int m, int S, int64_t T, int
 // 4096 x 256 (512 resident): 1024 (2.5) 204 us, 1408 (1.9) 210, 2048 (1.25) 220,
 // 4096 250.
 //
-// The queue packs the items of both passes and ends on part of one.  Whole calls,
+// The queue packs the items of both passes, ends on part of one, and has its
+// words cleared by a kernel first (7 x 33329 x 296, position-level, one round of
+// items either way: 90, 79 us).  Whole calls,
 // queue and launches in us (bf16, 128 wide): 288 x 8192 x 256 365, 361; 384 x
 // 32768 x 320 2119, 2098; 96 x 44045 x 368 876, 882; 288 x 16384 x 512 1190, 1194;
 // 320 x 4096 x 256 219, 204; 8 x 8192 x 256 73, 41; eight waves: 384 x 1000 x 512
@@ -200,8 +202,8 @@ ScoreForm choose_form(const ScorePlan& p, int queue_resident, int resident) {
       const uint64_t items = (uint64_t)groups * ((T + q - 1) / q);
       const uint64_t work = half ? items * 3 / 4 : items;
       const uint64_t fill = work > (uint32_t)queue_resident ? work : (uint32_t)queue_resident;
-      const uint64_t cost =
-          4 * fill * (c + kItemTokens) * res / (uint32_t)queue_resident + c / 4 * res;
+      const uint64_t cost = 4 * fill * (c + kItemTokens) * res / (uint32_t)queue_resident +
+                            (c / 4 + 2 * kItemTokens) * res;
       if (cost < best) {
         best = cost;
         f.chunk_tokens = (int)q;

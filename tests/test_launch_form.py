@@ -60,6 +60,8 @@ def test_every_form_fits_its_workspace(form):
     (32, 8, 4, 16, 65536, (1024, 2304), True),
     (8, 8, 1, 1, 131072, (1024, 2304), False),
     (32, 8, 4, 32, 65536, (1024, 1024), True),
+    (7, 1, 4, 125, 33329, (256, 256), False),     # one round either way
+    (48, 8, 4, 128, 1000, (256, 256), True),
 ])
 def test_known_forms(form, L, Hkv, G, m, T, resident, queue):
     lay = form.layout(L, G * Hkv, Hkv, 128, m, T)
